@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 
 PEAK_VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9   # CUs x SIMDs x lanes x clock: int32 VALU lane-ops/s
 OPS_PER_LOOKUP = 3.0                          # Eq. 3 lookup: form the R index, add the two bases and R, max
-OPS_PER_TERM = 2.0                            # add + max of one Eq. 1 term
+OPS_PER_TERM = 0.5                            # an Eq. 1 term inside a tile: 16 operations move and test the slacks of 32 splits
 # algorithmic HBM bytes of a lookup when the packed words (int16 base + 8-bit
 # difference vector, one per row and one per column of a group) are reused
 # over a 64 x 64-cell tile: 2 x 3 bytes per 64 lookups
@@ -212,10 +212,7 @@ def fold_work(n: int, q: int):
         between = (B - 3) * (B - 2) / 2 if B >= 4 else 0          # sum over d = 4..B of d - 3
         ends = 2 * B - 3 if B >= 2 else 0                         # sum over d = 1..B of min(d - 1, 2)
         lookups += (between + ends) * G * T * v
-        own_rows = v * 8 * 28 if 8 % q == 0 else v * T * (T - 1) / 2
-        block = v * 8 * 28 * (8 // q) if 8 % q == 0 else 0
-        lookups += B * block
-        terms += B * (T * v * (v - 1) / 2 + own_rows + T * v)
+        terms += B * (T * v * (v - 1) / 2 + v * T * (T - 1) / 2 + T * v)
         cells_out += B * T * v
     return lookups, terms, cells_out
 

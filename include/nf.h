@@ -314,12 +314,10 @@ int nf_autotune(int n, int qmin, int qmax, int reps);
  * diagonal and the between-group chunks of the next); the fill runs in the
  * execution its workspace uses (see nf_fold).  For every class:
  * lookups[k] counts the Four-Russians steps of Eq. 3 on table cells (padding
- * excluded): the groups between the end tiles, those of the two end tiles,
- * and, when q divides 8, the groups of each finished 8-row block of a tile
- * for the rows above it; splits[k] the terms of Eq. 1 evaluated one by one
- * (split points within a tile's own columns, those within its own rows that
- * are not looked up, plus the pairing term); cells[k] the table cells
- * finished.  Synchronous. */
+ * excluded): the groups between the end tiles and those of the two end tiles;
+ * splits[k] the terms of Eq. 1 inside a tile (split points within its own
+ * columns and its own rows, which the finish covers 32 at a time, plus the
+ * pairing term); cells[k] the table cells finished.  Synchronous. */
 typedef struct {
     int64_t launches[4];
     double ms[4];

@@ -62,27 +62,6 @@ __device__ __forceinline__ uint32_t r_index_s(uint32_t rw, uint32_t cw)
     return idx;
 }
 
-// The same with both words in vector registers.
-__device__ __forceinline__ uint32_t r_index_v(uint32_t rw, uint32_t cw)
-{
-    uint32_t idx;
-    __asm__("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:WORD_1"
-            : "=v"(idx)
-            : "v"(rw), "v"(cw));
-    return idx;
-}
-
-// max of a and the low 16 bits of b (as an unsigned number), one VALU
-// instruction (SDWA selects the low half of b).
-__device__ __forceinline__ int max_lo16(int a, uint32_t b)
-{
-    int d;
-    __asm__("v_max_i32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-            : "=v"(d)
-            : "v"(a), "v"(b));
-    return d;
-}
-
 // max of the low 16 bits of a, b and c as unsigned numbers, one VALU
 // instruction (the high halves of the operands are ignored).
 __device__ __forceinline__ uint32_t max3_u16(uint32_t a, uint32_t b, uint32_t c)
@@ -225,11 +204,112 @@ __global__ void k_copy_codes(const uint8_t* __restrict__ src, int n, uint8_t* __
     if (e < padded) dst[e] = e < n ? (src[e] & 3) : 0;
 }
 
-// Main-diagonal tiles (A, A): every split point lies inside the tile, so the
-// tile is filled by its own diagonals t = b - a = 2..T-1 (Eq. 1 directly).
+// ---- Rows in bits.
+//
+// A row of the table differs from the row below it by 0 or 1 in every column
+// (Lemma 1), so a tile is finished row by row, bottom-up, as one bit per cell:
+// delta(i, j) = X(i, j) - X(i+1, j).  With U(j', j) = F(BT+j', BT+j) (tile
+// (B, B)) let
+//     E(j', j) = X(i+1, j) - X(i+1, j') - U(j', j)            (j' < j)
+// be the slack of the split at j' on the row below: >= 0, since j' is a split
+// of Eq. 1.  A split at j' gives delta(i, j) = 1 exactly when delta(i, j') = 1
+// and E(j', j) = 0, a pairing (i, j) exactly when E(j-1, j) = 0 (then
+// X(i+1, j-1) + 1 > X(i+1, j)).  Eq. 1 makes F superadditive, so "E = 0" is
+// transitive and one pass closes a set of columns that rise by themselves
+// over all splits:  delta(j) = s(j) or (some j' in s with E(j', j) = 0).
+// Afterwards E(j', j) += delta(i, j) - delta(i, j').
+// The splits inside tile A are the same thing along the column: the slack
+//     V(i', j) = X(i+1, j) - X(i', j) - L(i+1, i'),   L(i, i') = F(AT+i, AT+i'),
+// gives delta(i, j) = 1 when V = 0 and dL(i, i') = L(i, i') - L(i+1, i') = 1,
+// and moves by delta(i, j) - dL(i, i').
+//
+// The slacks are bit-sliced: bit b of word p_k of a lane is bit k of the slack
+// at split point b (slacks are at most 63, so six words), and the +1/-1/0 of
+// a row is a ripple through the six words, two instructions each, for 32
+// split points at once.  A row therefore costs about 30 VALU instructions
+// per 32 split points and 64 lanes and no LDS access on its chain, where the
+// max-plus closure over 8 wavefronts it replaces took 27 instructions in each
+// of the 8, an LDS round trip and a barrier.
+
+// f(a, b, c) bit by bit, one instruction: kTable = f(0xF0, 0xCC, 0xAA).
+template <int kTable>
+__device__ __forceinline__ uint32_t bits3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, kTable & 0xff);
+}
+constexpr int kA = 0xF0, kB = 0xCC, kC = 0xAA;  // the three operands in a table
+
+// Slacks of 32 split points (one per bit) in one lane.
+struct Slack {
+    uint32_t p[6];
+    uint32_t nz;  // the OR of p: bit b is 0 where the slack is 0
+
+    __device__ __forceinline__ void test()
+    {
+        nz = bits3<kA | kB | kC>(bits3<kA | kB | kC>(p[0], p[1], p[2]), bits3<kA | kB | kC>(p[3], p[4], p[5]), 0u);
+    }
+    // at the bits of c: + 1 where up is all ones, - 1 where it is 0
+    __device__ __forceinline__ void step(uint32_t c, uint32_t up)
+    {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const uint32_t carry = bits3<kA & ~(kB ^ kC)>(c, p[k], up);
+            p[k] ^= c;
+            c = carry;
+        }
+        p[5] ^= c;
+        test();
+    }
+};
+
+// bit `pos` of x as a mask (all ones or 0), one instruction
+__device__ __forceinline__ uint32_t bit_mask(uint32_t x, uint32_t pos)
+{
+    return (uint32_t)__builtin_amdgcn_sbfe((int)x, pos, 1u);
+}
+
+// lane kLane of `old` replaced by the scalar v
+template <int kLane>
+__device__ __forceinline__ uint32_t with_lane(uint32_t old, uint32_t v)
+{
+    __asm__("v_writelane_b32 %0, %1, %2" : "+v"(old) : "s"(v), "n"(kLane));
+    return old;
+}
+
+// f(7), f(6), ..., f(0), each with its number as a constant
+template <int r = 7, class F>
+__device__ __forceinline__ void rows8(F&& f)
+{
+    f(std::integral_constant<int, r>{});
+    if constexpr (r > 0) rows8<r - 1>(f);
+}
+
+// For each of the 64 rows of a lane's code (S_{a+1} of row `lane`), the rows
+// whose base pairs with cb: bit i of the result.
+__device__ __forceinline__ unsigned long long pair_rows(int code, int cb)
+{
+    const unsigned long long m0 = __ballot(code == 0), m1 = __ballot(code == 1), m2 = __ballot(code == 2),
+                             m3 = __ballot(code == 3);
+    return cb == 0 ? m3 : (cb == 1 ? m2 : (cb == 2 ? m1 : m0));
+}
+
+// What a main-diagonal tile (B, B) keeps in the fold's blocks of packed words
+// (which hold no words for it): the slack words of tile column B, written by
+// the finish of (A+1, B) and read and updated by the finish of (A, B) one
+// step later, and the bits dL(i, .) of its own rows.  Three words of slack
+// and one half of every row's bits lie in the row block, the others in the
+// column block: 448 words in each, what a block holds at q = 9.
+//   word k of column j, split points 32h .. 32h+31: [(k % 3) * 128 + 2j + h]
+//   dL(i, i' < 32) in the row block at [384 + i], dL(i, i' >= 32) in the column block
+constexpr int kRowBits = 384;
+static_assert(row_words(9) >= kRowBits + 64 && state_words(9) >= kRowBits + 64, "the main-diagonal blocks hold the slacks");
+
+// Main-diagonal tiles (A, A): every split point lies inside the tile.  One
+// wavefront (lane j = column j) fills the tile by rows in bits (Eq. 1 needs
+// only the pairings and the splits E), the others wait for the emit.
 struct DiagLds {
-    int32_t X[64 * 65];  // padded stride 65: rows of a column are in distinct banks
-    uint8_t ca[64], cb[64];
+    unsigned long long cm[64];  // bit i of cm[j] = delta(i, j)
+    uint2 rows[64];             // rows[i] = dL(i, .)
 };
 
 //
@@ -244,18 +324,12 @@ template <int Q>
 __device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int tid, int nthr, const uint8_t* staged)
 {
     constexpr int T = tile_size(Q);
-    constexpr int XS = 65;
-    int32_t* X = s.X;
     const FoldDesc& f = it.f;
     const int aT = it.A * T;
     const bool admit = staged != nullptr && it.pad2 != 0;
     const uint8_t* src = admit ? staged + it.pad1 : f.codes;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
-    for (int e = tid; e < 64 * XS; e += nthr) X[e] = 0;
-    if (tid < 64) {
-        s.ca[tid] = src[aT + tid];                              // S_{a+1} for a = aT + i
-        s.cb[tid] = (aT + tid - 1 >= 0) ? src[aT + tid - 1] : 0;  // S_b for b = aT + j
-    }
     if (admit) {
         uint8_t* dst = const_cast<uint8_t*>(f.codes);
         const int hi = it.A == f.NT - 1 ? f.NT * T + 64 : aT + T;
@@ -264,36 +338,65 @@ __device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int ti
         int4* a1 = reinterpret_cast<int4*>(it.acc + (size_t)(f.NT + it.A) * kTileCells);
         for (int e = tid; e < kTileCells / 4; e += nthr) a0[e] = a1[e] = make_int4(0, 0, 0, 0);
     }
-    __syncthreads();
-
-    // diagonal t: cell (i, i+t) takes max over its split points m; eight
-    // lanes share a cell (lane k of the group takes m = i+1+k, i+9+k, ...)
-    // and combine their maxima inside the group with DPP (mirror within 8
-    // lanes, then two quad permutations).  Every value is >= 0, so 0 is the
-    // identity of max here.
-    const int grp = tid >> 3, sub = tid & 7, ngrp = nthr >> 3;
-    for (int t = 2; t < T; ++t) {
-        for (int i0 = 0; i0 < T - t; i0 += ngrp) {
-            const int i = i0 + grp;
-            const int j = i + t;
-            const bool live = i < T - t;
-            int v = 0;
-            if (live) {
-                for (int m = i + 1 + sub; m < j; m += 8) v = max(v, X[i * XS + m] + X[m * XS + j]);
-            }
-            v = max(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true));  // row_half_mirror
-            v = max(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
-            v = max(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));   // quad_perm [2,3,0,1]
-            if (live && sub == 0) X[i * XS + j] = max(v, (s.ca[i] + s.cb[j] == 3) + X[(i + 1) * XS + (j - 1)]);
+    if (wave == 0) {
+        const int j = lane;
+        const int ca = src[aT + j];                              // S_{a+1} for a = aT + lane
+        const int cb = (aT + j - 1 >= 0) ? src[aT + j - 1] : 0;  // S_b for b = aT + j
+        // split points below j; pairing rows i <= j - 2
+        const unsigned long long below = j < T ? (1ull << j) - 1 : 0ull;
+        unsigned long long pm = pair_rows(ca, cb) & (below >> 1);
+        const unsigned long long left = j > 0 ? 1ull << (j - 1) : 0ull;  // the slack a pairing needs
+        const uint32_t blo = (uint32_t)left, bhi = (uint32_t)(left >> 32);
+        const uint32_t vlo = (uint32_t)below, vhi = (uint32_t)(below >> 32);
+        Slack lo{}, hi{};
+        lo.p[5] = ~vlo;  // never 0 at split points that are not left of j
+        hi.p[5] = ~vhi;
+        lo.test();
+        hi.test();
+        unsigned long long cm = 0;
+        for (int b = 7; b >= 0; --b) {
+            const uint32_t pmb = (uint32_t)(pm >> (8 * b));
+            const unsigned long long pts = ~((256ull << (8 * b)) - 1);  // the split points of the blocks below
+            uint32_t rlo = 0, rhi = 0;  // lane r: dL(8b + r, .)
+            rows8([&](auto rc) {
+                constexpr int r = rc;
+                if (T < 64 && 8 * b + r >= T) return;
+                const uint32_t pb = bit_mask(pmb, r);
+                const unsigned long long st =
+                    __ballot(((bits3<~kA & kB>(lo.nz, blo, 0u) | bits3<~kA & kB>(hi.nz, bhi, 0u)) & pb) != 0);
+                const unsigned long long cl =
+                    __ballot((bits3<~kA & kB>(lo.nz, (uint32_t)st, 0u) | bits3<~kA & kB>(hi.nz, (uint32_t)(st >> 32), 0u)) != 0);
+                const unsigned long long dl = st | cl;
+                const uint32_t up = (dl >> j) & 1 ? ~0u : 0u;
+                // split points i < j' < j move; j' = i joins with slack 0
+                const unsigned long long rm = pts | ((0xffull & (0xfeull << r)) << (8 * b));
+                lo.step(bits3<(kA ^ kB) & kC>(up, (uint32_t)dl, vlo & (uint32_t)rm), up);
+                hi.step(bits3<(kA ^ kB) & kC>(up, (uint32_t)(dl >> 32), vhi & (uint32_t)(rm >> 32)), up);
+                cm = (cm << 1) | (up & 1u);
+                rlo = with_lane<r>(rlo, (uint32_t)dl);
+                rhi = with_lane<r>(rhi, (uint32_t)(dl >> 32));
+            });
+            if (lane < 8) s.rows[8 * b + lane] = make_uint2(rlo, rhi);
         }
-        __syncthreads();
+        s.cm[j] = cm;
+        uint32_t* rs = f.RS + tile_index(f.NT, it.A, 0) * row_words(Q);
+        uint32_t* cs = f.CS + tile_index(f.NT, it.A, 0) * state_words(Q);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            uint32_t* o = (k < 3 ? rs : cs) + (k % 3) * 128 + 2 * j;
+            *reinterpret_cast<uint2*>(o) = make_uint2(lo.p[k], hi.p[k]);
+        }
+        const uint2 rw = s.rows[j];
+        rs[kRowBits + j] = rw.x;
+        cs[kRowBits + j] = rw.y;
     }
+    __syncthreads();
 
     int16_t* F = f.F;
     const long long ld = f.ld;
-    for (int e = tid; e < 64 * 64; e += nthr) {
-        const int i = e >> 6, j = e & 63;
-        if (i < T && j < T) F[(aT + i) * ld + aT + j] = (int16_t)X[i * XS + j];
+    if (lane < T) {
+        const unsigned long long cm = s.cm[lane];
+        for (int i = wave; i < T; i += nthr / 64) F[(aT + i) * ld + aT + lane] = (int16_t)__popcll(cm >> i);
     }
 }
 
@@ -360,673 +463,252 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 
 // Finish of an off-diagonal tile (A, B), B > A, by 8 wavefronts (512 threads).
 //
-// Inside the tile, with L(i, i') = F(AT+i, AT+i') (tile (A, A)) and
-// U(j', j) = F(BT+j', BT+j) (tile (B, B)), cell X(i, j) = F(AT+i, BT+j) is
-//     max{ P(i, j),                                 between groups, in acc
-//          b(S_{a+1}, S_b) + X(i+1, j-1),            pairing
-//          max_{i < i' < T} L(i, i') + X(i', j),     splits inside tile A
-//          max_{0 <= j' < j} X(i, j') + U(j', j) }   splits inside tile B.
-// The last term only involves row i.  Eq. 1 makes F superadditive
-// (F(m1, m3) >= F(m1, m2) + F(m2, m3), since m2 is one of its split points),
-// so chains of U terms never beat a single one and the row recurrence has the
-// closed form  X(i, .) = Q(i, .) (max,+) (I + U),  Q = the first three terms.
-// Rows are finished bottom-up, one max-plus vector-matrix product per row.
+// Cell X(i, j) = F(AT+i, BT+j) is the maximum of P(i, j), the best split in
+// the tiles strictly between A and B (the between maxima of acc and the
+// groups of the two end tiles C = A+1, C = B-1), the pairing term, and the
+// splits inside tiles A and B.  P is computed first (8 rows per wavefront,
+// Eq. 3 lookups); the rows then go bottom-up in bits, as above: a cell rises
+// over the one below when P does, when a pairing or a split inside the tile
+// says so.  The row below row T-1 is row 0 of tile (A+1, B), finished one
+// step ago (or of the main-diagonal tile), and the slacks E carry over from
+// there, so no step rebuilds them; V starts empty at the tile's last row.
 //
-// Work split: wave w owns the 8 columns J_w = [8w, 8w+8) of every row.  Lane
-// l = 8g + c holds column j = 8w + c and the accumulators of the rows
-// i = 8b + g (b = 0..7: one row in each 8-row block), and for the closure it
-// reduces the split points j' in [8g, 8g+8) (its 8 entries of U sit in
-// registers); the 8 lanes of a column then combine their partial maxima with
-// a butterfly inside the wavefront (DPP row rotation and the gfx950 16/32-lane
-// swaps).  Each row costs one workgroup barrier: the row's Q is published in
-// LDS before it, the row's cells and the next row's Q after it.  The pairing
-// partner of the first column of a slice lives in the wavefront to the left,
-// so that one term is added by the readers of Q instead.
-//
-// A finished row is pushed (its L terms) into the rows above it in its 8-row
-// block, one split each, by the lanes that hold those rows; when a whole
-// block is finished and q divides 8 its q-groups reach every row above the
-// block through one R lookup per group (Eq. 3: row words of tile (A, A),
-// column words of this tile).  For other q every row is pushed into every row
-// above it one split at a time.  The groups of the two end tiles (C = A+1,
-// C = B-1) for the rows of block b-1 are looked up while block b is closed,
-// a few per row, in the slack of the row steps.
+// The rows are taken by four wavefronts, 16 columns each.  Lane 16h + c of
+// wavefront w holds column 16w + c and the split points 16h .. 16h+15 of both
+// kinds: E in the low half of its slack words, V in the high half, so that one
+// ripple moves both.  A wavefront works 8 rows (a block) behind its left
+// neighbour, from which it needs the rows' delta bits only; a barrier
+// separates the blocks.  (MI355X, against the max-plus closure by all eight
+// wavefronts: n = 6000 1.90 -> 1.49 ms, 4096 folds of 50..2000 bases
+// 16.9 -> 11.2 ms.)
 constexpr int kTileThreads = 512;
-static_assert(kTileThreads == 512, "the tile finish maps 8 wavefronts onto 8 column slices");
-constexpr int kNeg = -(1 << 20);  // stands for minus infinity; sums stay far from overflow
+constexpr int kChainWaves = 4;
+static_assert(kTileThreads == 512, "the tile finish maps 8 wavefronts onto 8 row blocks");
 
 template <int Q>
-__device__ __forceinline__ int rlookup(const uint8_t* Rl, uint32_t rw, uint32_t cw)
-{
-    return (int)((rw & 0xffffu) + (cw & 0xffffu)) + (int)Rl[(rw >> 16) + (cw >> 16)];
-}
-
-// The Eq. 3 term of a row word and a column word in the low 16 bits of the
-// result (the whole words are added: the term is one split of a cell, so it
-// stays below 2^15 and nothing carries out of the low half; the high half is
-// not meaningful).  Both words in vector registers.
-__device__ __forceinline__ uint32_t rterm(const uint8_t* Rl, uint32_t rw, uint32_t cw)
-{
-    return rw + cw + (uint32_t)Rl[r_index_v(rw, cw)];
-}
-
-// max of v over the 8 lanes l ^ {8, 16, 32} (lanes 8g + c, g = 0..7)
-__device__ __forceinline__ int max_over_groups(int v)
-{
-    v = max(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true));  // row_ror:8 = lane ^ 8 (every lane valid)
-    // the swaps return unsigned words: compare them as signed (-inf is negative)
-    auto p16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);           // {v[l], v[l ^ 16]}
-    v = max((int)p16[0], (int)p16[1]);
-    auto p32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);           // {v[l], v[l ^ 32]}
-    return max((int)p32[0], (int)p32[1]);
-}
-
-// kLean: the finish's lean form for the wide fused step (fewer registers and
-// less LDS): finished cells kept as 16-bit values and the end tiles' column
-// words read from LDS a row step ahead instead of held in registers.
-// The 7 difference bits of 8 values that fall by 0 or 1 from each to the
-// next (a column of the table going down, Lemma 1): bit p-1 is
-// x[p-1] - x[p].  As integers that is the sum over p of
-// (x[p-1] - x[p]) 2^(p-1) = x0 + x1 + 2 x2 + 4 x3 + 8 x4 + 16 x5 + 32 x6 - 64 x7,
-// formed here as a tree of shift-adds three deep (7 instructions instead of
-// a compare, a select and an or per bit).
-__device__ __forceinline__ uint32_t drop_bits8(const int (&x)[8])
-{
-    const int t0123 = (x[0] + x[1]) + ((x[2] + (x[3] << 1)) << 1);
-    const int t4567 = (x[4] + (x[5] << 1)) + ((x[6] - (x[7] << 1)) << 2);
-    return (uint32_t)(t0123 + (t4567 << 3));
-}
-
-template <int Q, bool kLean>
 struct TileLds {
-    static constexpr int G = groups_per_tile(Q);
-    static constexpr bool kBlockFR = (8 % Q) == 0;  // q-groups tile the 8-row blocks
-    static constexpr bool kStageEdges = G <= 16;    // end-tile words fit in LDS
-    using Cell = typename std::conditional<kLean, int16_t, int32_t>::type;
-    Cell Xs[64 * 64];  // finished cells, row-major (values < 2^15)
-    // Lp[i*kLS + 8g + b] = L(8b+g, i) for 8b+g < i < T, else -inf; the row
-    // stride keeps 16-byte rows and spreads the transposed writes over the
-    // banks.  The lean form keeps 16-bit values (-2^15 for -inf: a push of
-    // it stays below every cell) to make room for its Q slots.
-    using LCell = typename std::conditional<kLean, int16_t, int32_t>::type;
-    static constexpr int kLS = kLean ? 72 : 68;
-    LCell Lp[64 * kLS];
-    uint32_t LW[kBlockFR ? G * 64 : 4];  // LW[k*64 + 8g + b]: row word of row 8b+g, group k, tile (A, A)
-    uint32_t EB[kStageEdges ? 2 * G * 64 : 1];  // EB[(e*G + k)*64 + row] = row word, end tile e
-    uint32_t EC[kStageEdges ? 2 * G * 64 : 1];  // EC[(e*G + k)*64 + col] = column word, end tile e
-    // Q of the row being closed (double-buffered).  16-bit where every
-    // column of the tile is a cell (T = 64): the closure then runs on packed
-    // pairs.  With fewer posts the padding columns' values are not bounded
-    // by a cell, so those q keep 32-bit values.
-    static constexpr bool kPacked = tile_size(Q) == 64;
-    using QCell = typename std::conditional<kPacked, int16_t, int32_t>::type;
-    // Each of the 8 lane groups has a slot, so that every lane writes its
-    // candidate and the row's chain has no masked write (the readers take the
-    // slot of the row's group).
-    // (slots 144 or 272 bytes apart: the 8 lanes that write one column's
-    // slots hit 8 different banks, and rows stay 16-byte aligned)
-    static constexpr int kQS = kPacked ? 72 : 68;
-    alignas(16) QCell Qs[2][8][kQS];
-    int32_t hrow[64];
-    alignas(16) int32_t hcT[64];  // hcT[8g + b] = halo partner of column 0 in row 8b + g
-    alignas(16) uint8_t caT[64];  // caT[8g + b] = S_{a+1} of row 8b + g
-    uint8_t ca[64], cb[64];
-    unsigned long long GM[8];  // GM[g] bit i: pairing of (row i, column 8g)
+    // M[h][i]: bits 31..16 = dL(i, 16h .. 16h+15); bits 15..0 = delta(i, .) of
+    // the columns 16h .. 16h+15 once finished (h = 3 first holds, in bit 15,
+    // delta of the column left of the tile, for column 0)
+    alignas(16) uint32_t M[4][64];
+    alignas(16) uint16_t P[8][64][8];  // P(i, j) at [i / 8][j][i % 8]
+    uint32_t cm[2][64];                // delta(32 u + b, j): bit b of cm[u][j]
+    int32_t top[64];                   // X(T, j): the row below row T-1
 };
 
-// The finish of one tile by kTileThreads threads.  With kLoadR the finish
-// copies R from Rg (global) into Rl itself; otherwise Rl already holds it.
-// wait_pre() runs before
-// the loads that need the main-diagonal tiles (A, A) and (B, B); wait_main()
-// before the loads that need the tiles of diagonal d-1 and the between-group
-// maxima.  Both are collective (every thread calls them).
-template <int Q, bool kLoadR, bool kLean, class Pre, class Main>
-__device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const uint8_t* Rg, TileLds<Q, kLean>& s,
-                                          Pre&& wait_pre, Main&& wait_main)
+// max(0, P - x) of the P in the low or high half of pair, nonzero when P > x
+// (one SDWA instruction; both are below 2^15)
+template <int kHalf>
+__device__ __forceinline__ uint32_t above(uint32_t pair, uint32_t x)
+{
+    uint32_t d;
+    if constexpr (kHalf == 0)
+        __asm__("v_sub_u16_sdwa %0, %1, %2 clamp dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_0"
+                : "=v"(d)
+                : "v"(pair), "v"(x));
+    else
+        __asm__("v_sub_u16_sdwa %0, %1, %2 clamp dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:WORD_0"
+                : "=v"(d)
+                : "v"(pair), "v"(x));
+    return d;
+}
+
+// The finish of one tile by kTileThreads threads.  R is copied from Rg
+// (global) into Rl.
+template <int Q>
+__device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const uint8_t* __restrict__ Rg,
+                                          TileLds<Q>& s)
 {
     constexpr int M = Q - 1;
     constexpr int G = groups_per_tile(Q);
     constexpr int T = tile_size(Q);
     constexpr int SW = state_words(Q);
     constexpr int RW = row_words(Q);
-    using Lds = TileLds<Q, kLean>;
-    using Cell = typename Lds::Cell;
-    constexpr bool kBlockFR = Lds::kBlockFR;
-    constexpr int GPB = kBlockFR ? 8 / Q : 1;  // groups per block
-    constexpr bool kStageEdges = Lds::kStageEdges;
-    constexpr int NE = kStageEdges ? 2 * G : 1;  // end-tile lookups per row (both edges)
-    static_assert(!kStageEdges || NE > 8, "every row's share of the end-tile groups is at least one");
-    constexpr int LS = Lds::kLS;
-    Cell* Xs = s.Xs;
-    typename Lds::LCell* Lp = s.Lp;
-    uint32_t* LW = s.LW;
-    uint32_t* EB = s.EB;
-    uint32_t* EC = s.EC;
-    using QCell = typename Lds::QCell;
-    QCell (*Qs)[8][Lds::kQS] = s.Qs;
-    int32_t* hrow = s.hrow;
-    int32_t* hcT = s.hcT;
-    uint8_t* caT = s.caT;
-    uint8_t* ca = s.ca;
-    uint8_t* cb = s.cb;
-    unsigned long long* GM = s.GM;
+    constexpr int RSZ = 1 << (2 * M);
 
     const FoldDesc& f = it.f;
     const int A = it.A, d = it.d, B = A + d;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
-    const int g = lane >> 3, c = lane & 7;
-    const int j = wave * 8 + c;  // this lane's column; its rows are 8b + g
     const long long ld = f.ld;
     const int aT = A * T, bT = B * T;
-    const NF_GLOBAL int16_t* F = (const NF_GLOBAL int16_t*)f.F;  // global loads: see the output pointers
+    const NF_GLOBAL int16_t* F = (const NF_GLOBAL int16_t*)f.F;
     const NF_GLOBAL uint8_t* codes = (const NF_GLOBAL uint8_t*)f.codes;
-    const NF_GLOBAL uint32_t* RSr = (const NF_GLOBAL uint32_t*)f.RS;
-    const NF_GLOBAL uint32_t* CSr = (const NF_GLOBAL uint32_t*)f.CS;
-    const int nedge = d >= 3 ? 2 : (d == 2 ? 1 : 0);
+    const NF_GLOBAL uint32_t* rsA = (const NF_GLOBAL uint32_t*)f.RS + tile_index(f.NT, A, 0) * RW;
+    const NF_GLOBAL uint32_t* csA = (const NF_GLOBAL uint32_t*)f.CS + tile_index(f.NT, A, 0) * SW;
+    NF_GLOBAL uint32_t* rsB = (NF_GLOBAL uint32_t*)f.RS + tile_index(f.NT, B, 0) * RW;
+    NF_GLOBAL uint32_t* csB = (NF_GLOBAL uint32_t*)f.CS + tile_index(f.NT, B, 0) * SW;
 
-    // ---- prologue.  Every global load is issued before the first LDS store
-    // (an LDS store of loaded data waits on the load counter, which drains in
-    // order), so the tile pays about one memory round trip here.
-    // part 1: R (when loading it), L, U and the codes
-    wait_pre();
-    constexpr int RSZ = 1 << (2 * M);
-    uint8_t rbyte = 0;
-    uint4 rvec = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (kLoadR) {
-        if constexpr (RSZ >= 1024) {
-            // R goes global -> LDS by DMA (no registers, no LDS store): lane l
-            // of a wave lands at the wave's base + 16 l.  One wave moves 1 KB,
-            // and RSZ is a multiple of 1 KB here, so no lane reads past R or
-            // writes past Rl.
+    // ---- set-up: R, the rows' bits of tile (A, A), the row below, the halo
+    load_R<RSZ>(Rl, Rg, kTileThreads);
+    if (tid < 256) {
+        const int h = wave, i = lane;
+        uint32_t m = (h < 2 ? rsA : csA)[kRowBits + i];
+        m = (h & 1) ? (m & 0xffff0000u) : (m << 16);
+        if (i >= T) m = 0;
+        if (h == 3 && i < T) {
+            // delta(i, -1); nothing lies below row T-1 left of tile (B, B)
+            const int up = F[(aT + i) * ld + bT - 1];
+            const int dn = (d == 1 && i == T - 1) ? 0 : (int)F[(aT + i + 1) * ld + bT - 1];
+            if (up > dn) m |= 1u << 15;
+        }
+        s.M[h][i] = m;
+    } else if (wave == 4) {
+        s.top[lane] = lane < T ? (int)F[(aT + T) * ld + bT + lane] : 0;
+    }
+
+    // the row wavefronts' own state
+    const int h = lane >> 4, c = lane & 15;
+    const int j = 16 * (wave & 3) + c;
+    Slack sl{};
+    uint32_t vr = 0, own = 0, left = 0;
+    unsigned long long pm = 0;
+    uint32_t x = 0;
+    if (wave < kChainWaves) {
+        typedef const NF_GLOBAL uint16_t* half_ptr;
+        // the split points of this lane left of column j
+        const uint32_t below = j >= T ? 0u : (j >= 16 * h + 16 ? 0xffffu : (j > 16 * h ? (1u << (j - 16 * h)) - 1 : 0u));
 #pragma unroll
-            for (int u = 0; u < (RSZ + kTileThreads * 16 - 1) / (kTileThreads * 16); ++u) {
-                const int base = (u * kTileThreads + wave * 64) * 16;  // wave-uniform
-                if (base < RSZ)
-                    __builtin_amdgcn_global_load_lds((const NF_GLOBAL void*)(Rg + base + lane * 16),
-                                                     (__attribute__((address_space(3))) void*)(Rl + base), 16, 0, 0);
-            }
-        } else if constexpr (RSZ >= 16) {
-            // 16 .. 256 bytes: one 16-byte load per lane that holds a piece,
-            // stored to LDS with the other prologue stores
-            if (tid * 16 < RSZ) {
-                const NF_GLOBAL uint32_t* src = (const NF_GLOBAL uint32_t*)(Rg + tid * 16);
-                rvec = make_uint4(src[0], src[1], src[2], src[3]);
-            }
+        for (int k = 0; k < 6; ++k)
+            sl.p[k] = ((half_ptr)(k < 3 ? rsB : csB))[(k % 3) * 256 + 4 * j + h] & below;
+        vr = below;
+        own = h == wave ? 0xffffu : 0u;
+        left = (j > 0 && ((j - 1) >> 4) == h) ? 1u << ((j - 1) & 15) : 0u;
+        pm = pair_rows(lane < T ? (int)codes[aT + lane] : 4, (int)codes[bT + j - 1]);
+        if (j >= T) pm = 0;
+        x = j < T ? (uint32_t)(int)F[(aT + T) * ld + bT + j] : 0u;
+        if (j == 0 && h == 3) {
+            // column 0: the column left of the tile is its split point -1, bit
+            // 15 here, with slack X(T, 0) - X(T, -1)
+            const int xl = d == 1 ? (int)x : (int)F[(aT + T) * ld + bT - 1];
+            sl.p[0] = ((int)x > xl) ? 1u << 15 : 0u;
+            vr = left = 1u << 15;
+        }
+        sl.p[5] |= 0xffffu & ~vr;      // never 0 where there is no split point
+        if (j >= T) sl.p[5] = ~0u;
+        sl.test();
+    }
+
+    // ---- P for the rows 8 wave .. 8 wave + 7, column `lane`
+    {
+        int acc[8];
+        const int r0 = 8 * wave;
+        NF_GLOBAL int32_t* accb = (NF_GLOBAL int32_t*)it.acc + r0 * 64;
+        if (it.nslot > 0) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) acc[r] = (accb + r * 64)[(unsigned)lane];
         } else {
-            rbyte = ((const NF_GLOBAL uint8_t*)Rg)[min(tid, RSZ - 1)];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) acc[r] = 0;
         }
-    }
-    // Addresses below are a wave-uniform base (scalar arithmetic) plus a
-    // 32-bit lane offset, so the loads need almost no vector instructions.
-    int lv[8];  // L(ip, lane) for the row ip = wave + 8u of tile (A, A), read coalesced
+        __syncthreads();  // R
+        if (d >= 2) between_accumulate<Q, 8, 1>(acc, Rl, f.RS, f.CS, f.NT, A, B, A + 1, A + 2, r0, lane, 0);
+        if (d >= 3) between_accumulate<Q, 8, 1>(acc, Rl, f.RS, f.CS, f.NT, A, B, B - 1, B, r0, lane, 0);
+        if (it.nslot > 0) {  // hand the accumulator back zeroed for its next use
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int ip = wave + 8 * u;
-        const NF_GLOBAL int16_t* Lrow = F + (long long)(aT + ip) * ld + aT;
-        lv[u] = (ip < lane && lane < T) ? (int)Lrow[(unsigned)lane] : kNeg;
-    }
-    int ureg[8];  // U(8g + t, j); -inf where the split point is not left of column j
-    const unsigned uoff = (unsigned)(8 * g) * (unsigned)ld + (unsigned)j;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const int jp = 8 * g + t;
-        const NF_GLOBAL int16_t* Urow = F + (long long)(bT + t) * ld + bT;
-        ureg[t] = (jp <= j && j < T) ? (int)Urow[uoff] : kNeg;
-    }
-    uint8_t cda = 0, cdb = 0;
-    if (tid < 64) {
-        cda = codes[aT + tid];      // S_{a+1}, a = AT + i
-        cdb = codes[bT + tid - 1];  // S_b,     b = BT + j  (BT >= 1)
-    }
-
-    // part 2: the between maxima, the end tiles and the halo
-    wait_main();
-    int acc[8];  // acc[b]: row 8b + g, column j
-    NF_GLOBAL int32_t* accb = (NF_GLOBAL int32_t*)it.acc;
-    const unsigned aoff = (unsigned)(g * 64 + j);
-    if (it.nslot > 0) {
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[b] = (accb + b * 512)[aoff];
-    } else {
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[b] = 0;
-    }
-    // edge e: C = A+1 (e = 0) and C = B-1 (e = 1); {base, bits} per row of
-    // tile (A, C), column words of tile (C, B).  An end tile that does not
-    // exist (e >= nedge) gets zero words: its lookups then give 0, which no
-    // accumulator is below, so every lookup can run unguarded.  (The loads
-    // stay inside the fold's tile arrays either way.)
-    constexpr int kIter = kStageEdges ? (2 * G * 64 + kTileThreads - 1) / kTileThreads : 1;
-    uint32_t rb[kIter], cw[kIter];
-    if constexpr (kStageEdges) {
-#pragma unroll
-        for (int u = 0; u < kIter; ++u) {
-            const int eg = wave + u * (kTileThreads / 64);  // (tid + u * kTileThreads) >> 6, wave-uniform
-            const int e = eg / G, k = eg - e * G;
-            const int C = e == 0 ? A + 1 : B - 1;
-            rb[u] = cw[u] = 0;
-            if (eg < 2 * G) {
-                rb[u] = (RSr + tile_index(f.NT, A, C - A) * RW + k * 64)[(unsigned)lane];
-                cw[u] = (CSr + tile_index(f.NT, C, B - C) * SW + k * 64)[(unsigned)lane];
-            }
+            for (int r = 0; r < 8; ++r) (accb + r * 64)[(unsigned)lane] = 0;
         }
+        uint4 pk = make_uint4((uint32_t)acc[0] | ((uint32_t)acc[1] << 16), (uint32_t)acc[2] | ((uint32_t)acc[3] << 16),
+                              (uint32_t)acc[4] | ((uint32_t)acc[5] << 16), (uint32_t)acc[6] | ((uint32_t)acc[7] << 16));
+        if (lane >= T) pk = make_uint4(0u, 0u, 0u, 0u);
+        *reinterpret_cast<uint4*>(&s.P[wave][lane][0]) = pk;
     }
-    int hrv = 0, hcv = 0;
-    if (tid < T) {
-        const int hr_r = aT + T, hr_c = bT - 1 + tid;  // F((A+1)T, BT-1+j)
-        if (hr_c >= hr_r) hrv = F[hr_r * ld + hr_c];
-        const int hc_r = aT + 1 + tid, hc_c = bT - 1;  // F(AT+1+i, BT-1)
-        if (hc_c >= hc_r) hcv = F[hc_r * ld + hc_c];
-    }
-
-    // stores
-    if constexpr (kLoadR && RSZ < 16) {
-        if (tid < RSZ) Rl[tid] = rbyte;
-    } else if constexpr (kLoadR && RSZ < 1024) {
-        if (tid * 16 < RSZ) *reinterpret_cast<uint4*>(Rl + tid * 16) = rvec;
-    }
-    if (tid < 64) {
-        ca[tid] = cda;
-        cb[tid] = cdb;
-        caT[(tid & 7) * 8 + (tid >> 3)] = cda;  // transposed: one 8-byte read per lane
-    }
-    if constexpr (kStageEdges) {
-#pragma unroll
-        for (int u = 0; u < kIter; ++u) {
-            const int x = tid + u * kTileThreads;
-            if (x < 2 * G * 64) {
-                const bool live = (x >> 6) < nedge * G;
-                EB[x] = live ? rb[u] : 0u;
-                EC[x] = live ? cw[u] : 0u;
-            }
-        }
-    }
-    if (tid < T) hrow[tid] = hrv;
-    if (tid < 64) hcT[(tid & 7) * 8 + (tid >> 3)] = hcv;  // hcv = 0 for rows >= T
-    // this thread holds L(8u + wave, lane), u = 0..7: eight consecutive words
-    if constexpr (kLean) {
-        auto h16 = [](int v) { return (uint32_t)(uint16_t)(int16_t)max(v, -32768); };
-        *reinterpret_cast<int4*>(&Lp[lane * LS + 8 * wave]) =
-            make_int4((int)(h16(lv[0]) | (h16(lv[1]) << 16)), (int)(h16(lv[2]) | (h16(lv[3]) << 16)),
-                      (int)(h16(lv[4]) | (h16(lv[5]) << 16)), (int)(h16(lv[6]) | (h16(lv[7]) << 16)));
-    } else {
-        *reinterpret_cast<int4*>(&Lp[lane * LS + 8 * wave]) = make_int4(lv[0], lv[1], lv[2], lv[3]);
-        *reinterpret_cast<int4*>(&Lp[lane * LS + 8 * wave + 4]) = make_int4(lv[4], lv[5], lv[6], lv[7]);
-    }
-    if (it.nslot > 0) {  // hand the accumulator back zeroed for its next use
-#pragma unroll
-        for (int b = 0; b < 8; ++b) (accb + b * 512)[aoff] = 0;
-    }
-    if constexpr (kLoadR && RSZ >= 1024) __builtin_amdgcn_s_waitcnt(0);  // the R transfer (vector memory counter) is done
     __syncthreads();
 
-    // ---- row words of tile (A, A) for the block pushes
-    if constexpr (kBlockFR) {
-        for (int x = tid; x < G * 64; x += kTileThreads) {
-            const int k = x >> 6, pos = x & 63;       // pos = 8g' + b'
-            const int r = (pos & 7) * 8 + (pos >> 3);  // row 8b' + g'
-            const int top = k * Q;
-            uint32_t h = 0;
-            int base = 0;
-            if (top > r && top < T) {
-                base = Lp[top * LS + pos];
-                if constexpr (Q == 8) {
-                    // along a row the values rise by 0 or 1 (Lemma 1)
-                    int v[8];
-#pragma unroll
-                    for (int p = 0; p < 8; ++p) v[p] = Lp[(top + p) * LS + pos];
-                    h = 0u - drop_bits8(v);
-                } else {
-#pragma unroll
-                    for (int p = 1; p <= M; ++p)
-                        h |= (uint32_t)(Lp[(top + p) * LS + pos] > Lp[(top + p - 1) * LS + pos]) << (p - 1);
+    // ---- rows bottom-up, block b = 7 - (phase - wave) of 8 rows
+    uint32_t cml = 0, cmh = 0;
+    for (int phase = 0; phase < 8 + kChainWaves - 1; ++phase) {
+        const int b = 7 - (phase - wave);
+        if (wave < kChainWaves && b >= 0 && b < 8) {
+            const uint4 pk = *reinterpret_cast<const uint4*>(&s.P[b][j][0]);
+            const uint4 ma = *reinterpret_cast<const uint4*>(&s.M[h][8 * b]);
+            const uint4 mb = *reinterpret_cast<const uint4*>(&s.M[h][8 * b + 4]);
+            const uint32_t ps[4] = {pk.x, pk.y, pk.z, pk.w};
+            const uint32_t ms[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+            const uint32_t pmb = (uint32_t)(pm >> (8 * b));
+            const uint32_t rmask = (h == (b >> 1) && j < T) ? ~0u : 0u;  // lanes that hold the split points of this block
+            uint32_t bit = 1u << (16 + (b & 1) * 8 + 7);
+            uint32_t rows = 0;  // lane r: delta(8b + r, .) of this wavefront's columns
+            uint32_t cm8 = 0;
+            rows8([&](auto rc) {
+                constexpr int r = rc;
+                if (T == 64 || 8 * b + r < T) {
+                    const uint32_t up_p = above<r & 1>(ps[r >> 1], x);
+                    const uint32_t cand = bits3<kA | (kB & kC)>(ms[r], bit_mask(pmb, r), left);
+                    const unsigned long long b1 = __ballot(bits3<(~kA & kB) | kC>(sl.nz, cand, up_p) != 0);
+                    const uint32_t t1 = (uint32_t)b1 | (uint32_t)(b1 >> 32);
+                    const uint32_t st = t1 | (t1 >> 16);
+                    const unsigned long long b2 = __ballot(bits3<~kA & kB & kC>(sl.nz, st, own) != 0);
+                    const uint32_t dl = st | (uint32_t)(b2 >> (16 * wave));
+                    const uint32_t up = bit_mask(dl, c);
+                    const uint32_t mv = bits3<kA | (kB & kC)>(ms[r], dl, own);
+                    sl.step(bits3<(kA ^ kB) & kC>(up, mv, vr), up);
+                    vr = bits3<kA | (kB & kC)>(vr, rmask, bit);
+                    x -= up;
+                    cm8 = __builtin_amdgcn_alignbit(cm8, up, 31);
+                    rows = with_lane<r>(rows, dl);
                 }
-            }
-            LW[x] = ((h << M) << 16) | (uint32_t)base;
+                bit >>= 1;
+            });
+            cmh = __builtin_amdgcn_alignbit(cmh, cml, 24);
+            cml = (cml << 8) | cm8;
+            // the block's bits for the wavefronts to the right and the emit
+            if (lane < 8) reinterpret_cast<uint16_t*>(&s.M[wave][8 * b + lane])[0] = (uint16_t)rows;
         }
+        __syncthreads();
     }
-
-    // column words of the end tiles at this lane's column (fixed for the
-    // tile): in registers, or in the lean form read from LDS where used
-    constexpr int NEC = (kStageEdges && !kLean) ? NE : 1;
-    uint32_t ecw[NEC];
-    if constexpr (kStageEdges && !kLean) {
-#pragma unroll
-        for (int x = 0; x < NE; ++x) ecw[x] = EC[x * 64 + j];
-    }
-    auto col_word = [&](int x) -> uint32_t {
-        if constexpr (kStageEdges && !kLean) return ecw[x];
-        else return EC[x * 64 + j];
-    };
-    // one end-tile lookup (edge e, group k: x = e*G + k) for row 8b + g and
-    // this lane's column
-    // (low 16 bits of the result, see rterm)
-    auto edge = [&](int x, int b) { return rterm(Rl, EB[x * 64 + 8 * b + g], col_word(x)); };
-
-    if constexpr (kStageEdges) {
-        // rows of block 7 take their end-tile groups here, the other blocks
-        // inside the row loop (NE = 2G is even)
-        const uint32_t e0 = edge(0, 7);
-        uint32_t e16 = max3_u16(e0, edge(1, 7), e0);
-#pragma unroll
-        for (int x = 2; x < NE; x += 2) e16 = max3_u16(e16, edge(x, 7), edge(x + 1, 7));
-        acc[7] = max_lo16(acc[7], e16);
-    } else {
-        // q < 4: the end tiles' words are read straight from memory
-        for (int e = 0; e < nedge; ++e) {
-            const int C = e == 0 ? A + 1 : B - 1;
-            const NF_GLOBAL uint32_t* rs = RSr + tile_index(f.NT, A, C - A) * RW;
-            const NF_GLOBAL uint32_t* cs = CSr + tile_index(f.NT, C, B - C) * SW;
-            for (int k = 0; k < G; ++k) {
-                const uint32_t cw = cs[k * 64 + j];
-#pragma unroll
-                for (int b = 0; b < 8; ++b) acc[b] = max(acc[b], rlookup<Q>(Rl, rs[k * 64 + 8 * b + g], cw));
-            }
+    if (wave < kChainWaves) {
+        if (h == 0) {
+            s.cm[0][j] = cml;
+            s.cm[1][j] = cmh;
         }
+        typedef NF_GLOBAL uint16_t* half_out;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) ((half_out)(k < 3 ? rsB : csB))[(k % 3) * 256 + 4 * j + h] = (uint16_t)sl.p[k];
     }
+    __syncthreads();
 
-    // pairing bits of this lane's rows; pairing terms whose partner lies
-    // outside the tile (last row, first column) come from the halo
-    const int cbj = cb[j];
-    uint32_t pmask = 0;
-    {  // pairing mask of slice-start column 8*wave, by ballot over rows
-        const unsigned long long m = __ballot(ca[lane] + (int)cb[wave * 8] == 3);
-        if (lane == 0) GM[wave] = m;
-    }
-    const int hrj = hrow[j];
-    int cai[8], hci[8];
-    {
-        const unsigned long long cw8 = *reinterpret_cast<const unsigned long long*>(&caT[8 * g]);
-        const int4 ha = *reinterpret_cast<const int4*>(&hcT[8 * g]);
-        const int4 hb = *reinterpret_cast<const int4*>(&hcT[8 * g + 4]);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) cai[b] = (int)((cw8 >> (8 * b)) & 0xffu);
-        hci[0] = ha.x; hci[1] = ha.y; hci[2] = ha.z; hci[3] = ha.w;
-        hci[4] = hb.x; hci[5] = hb.y; hci[6] = hb.z; hci[7] = hb.w;
-    }
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const int i = 8 * b + g;
-        const int bp = (i < T && j < T && cai[b] + cbj == 3) ? 1 : 0;
-        pmask |= (uint32_t)bp << b;
-        const int halo = (i == T - 1) ? hrj : hci[b];  // the last row's partner first, then column 0's
-        if (i < T && j < T && (i == T - 1 || j == 0)) acc[b] = max(acc[b], bp + halo);
-    }
-    // the pairing bias of row 8b + g at column j for its Q: the bit, or
-    // -inf where the partner X(i, j-1) is in another wavefront (c = 0: the
-    // readers add that term)
-    int pbv[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) pbv[b] = c > 0 ? (int)((pmask >> b) & 1u) : kNeg;
-
-    // outputs: dense cells, row words, column words, written after the row
-    // loop (global address space: generic
-    // accesses also count against the LDS counter that barriers wait on)
+    // ---- emit: dense cells, row words, column words; wavefront w takes the
+    // rows 8w .. 8w+7, lane = column
     const long long t_idx = tile_index(f.NT, A, d);
     NF_GLOBAL int16_t* Fw = (NF_GLOBAL int16_t*)f.F;
     NF_GLOBAL uint32_t* RSw = (NF_GLOBAL uint32_t*)(f.RS + t_idx * RW);
     NF_GLOBAL uint32_t* CSw = (NF_GLOBAL uint32_t*)(f.CS + t_idx * SW);
-
-    // ---- rows bottom-up.  Rows >= T (only when T < 64) are inert: their
-    // pushes are -inf in Lp and their pairing into row T-1 is skipped.
-    // row 63: Q complete (no row below)
-    Qs[1][g][j] = (QCell)acc[7];  // (slot 7 is row 63's)
-    // U as pairs of 16-bit values for the packed closure, with -2^15 for
-    // minus infinity.  Every real sum Q(i, j') + U(j', j) is at most
-    // X(i, j) < 2^15 and Q >= 0, so no sum leaves the 16-bit range.  u0p is
-    // U(8g, j) for the pairing term, minus infinity also where g = 0 (that
-    // lane's term then stays <= 0, which no cell is below, and needs no
-    // select per row).
-    constexpr bool kPacked = Lds::kPacked;
-    uint32_t up[4] = {0u, 0u, 0u, 0u};
-    if constexpr (kPacked) {
-        auto h16 = [](int v) { return (uint32_t)(v < 0 ? 0x8000 : v); };
-#pragma unroll
-        for (int t = 0; t < 4; ++t) up[t] = h16(ureg[2 * t]) | (h16(ureg[2 * t + 1]) << 16);
-    }
-    const int u0p = (g > 0 && ureg[0] >= 0) ? ureg[0] : (kPacked ? -32768 : kNeg);
-    const int xlc = g > 0 ? 8 * g - 1 : 0;
-    // end-tile row and column words of the share of row (bb, r): groups
-    // x = r + 8m of block bb-1, loaded one row step ahead of their use
-    // (erw/erc: this row's, ern/ecn: the next row's, fetched while this row
-    // is closed)
-    constexpr int kEPer = (NE + 7) / 8;
-    uint32_t erw[kEPer], erc[kEPer], ern[kEPer], ecn[kEPer];
-    auto fetch_edges = [&](int bb, int r, uint32_t (&rw)[kEPer], uint32_t (&cw)[kEPer]) {
-#pragma unroll
-        for (int m = 0; m < kEPer; ++m) {
-            const int x = r + 8 * m;
-            const bool live = bb >= 1 && x < NE;
-            rw[m] = live ? EB[x * 64 + 8 * (bb - 1) + g] : 0u;
-            if constexpr (kLean) cw[m] = live ? EC[x * 64 + j] : 0u;
-        }
-    };
-    if constexpr (kStageEdges) fetch_edges(7, 7, erw, erc);
-    __syncthreads();
-    const unsigned long long gmask = GM[g];
-
-    uint32_t evb = 0;  // see edge_terms
-#pragma unroll
-    for (int blk = 7; blk >= 0; --blk) {
-#pragma unroll
-        for (int rr = 7; rr >= 0; --rr) {
-            const int i = blk * 8 + rr;
-            // ---- LDS loads of the row, issued together after the barrier:
-            // Q(i, 8g..8g+7), the pairing partner of column 8g, L(., i) for
-            // the pushes, and the end-tile words of this row's share of
-            // block blk-1
-            const int qslot = i & 7;  // the slot of row i's lane group (a constant once unrolled)
-            const int4 qa = *reinterpret_cast<const int4*>(&Qs[i & 1][qslot][8 * g]);  // 8 values (packed) or 4
-            int4 qb = make_int4(0, 0, 0, 0);
-            if constexpr (!kPacked) qb = *reinterpret_cast<const int4*>(&Qs[i & 1][qslot][8 * g + 4]);
-            int xl = kNeg;
-            // X(i+1, 8g-1); lanes of slice 0 read the finished X(i+1, 0)
-            // instead, so that their pairing term stays finite and, with
-            // u0p, below every cell
-            if (i < T - 1) xl = Xs[(i + 1) * 64 + xlc];
-            int lp[8];
-            if constexpr (kBlockFR) {
-                lp[blk] = Lp[i * LS + 8 * g + blk];
-            } else {
-                const int4 la = *reinterpret_cast<const int4*>(&Lp[i * LS + 8 * g]);
-                const int4 lb = *reinterpret_cast<const int4*>(&Lp[i * LS + 8 * g + 4]);
-                lp[0] = la.x; lp[1] = la.y; lp[2] = la.z; lp[3] = la.w;
-                lp[4] = lb.x; lp[5] = lb.y; lp[6] = lb.z; lp[7] = lb.w;
-            }
-            // The row's chain waits on Q: nothing below is issued before
-            // these reads, the end-tile gathers of this row's share (words
-            // fetched a row ahead) go out next with the next row's words, and
-            // their sums come after the closure (see edge_terms)
-            __builtin_amdgcn_sched_barrier(0);
-            uint32_t rg[kEPer];
-            if constexpr (kStageEdges) {
-                if (blk >= 1) {
-#pragma unroll
-                    for (int m = 0; m < kEPer; ++m) {
-                        const int x = rr + 8 * m;
-                        rg[m] = x < NE ? (uint32_t)Rl[r_index_v(erw[m], kLean ? erc[m] : col_word(x))] : 0u;
-                    }
-                }
-                fetch_edges(rr > 0 ? blk : blk - 1, rr > 0 ? rr - 1 : 7, ern, ecn);
-            }
-            // pairing of (i-1, j) with partner X(i, j-1), for the next row's
-            // Q: its bit, or -inf where there is no partner (formed here,
-            // off the chain)
-            const int pb = (i >= 1 && i < T) ? pbv[(i - 1) >> 3] : kNeg;
-            __builtin_amdgcn_sched_barrier(0);
-            // the end-tile terms of this row's share into the rows of block
-            // blk-1 (Eq. 3; the term's value in the low 16 bits, see rterm)
-            // The block's 8 row steps keep their terms in a running 16-bit
-            // maximum (evb), which goes into acc[blk-1] once, at the block's
-            // last row: nothing reads acc[blk-1] before that.
-            auto edge_terms = [&] {
-                if constexpr (kStageEdges) {
-                    if (blk >= 1) {
-                        uint32_t ev = evb;
-#pragma unroll
-                        for (int m = 0; m < kEPer; m += 2) {
-                            const int m1 = m + 1 < kEPer ? m + 1 : m;
-                            const int x0 = rr + 8 * m, x1 = rr + 8 * (m + 1);
-                            if (x0 >= NE) continue;  // x0 = rr < 8 < NE when m = 0
-                            const uint32_t t0 = erw[m] + (kLean ? erc[m] : col_word(x0)) + rg[m];
-                            const uint32_t t1 = (m + 1 < kEPer && x1 < NE)
-                                                    ? erw[m1] + (kLean ? erc[m1] : col_word(x1)) + rg[m1]
-                                                    : t0;
-                            ev = max3_u16((m == 0 && rr == 7) ? t0 : ev, t0, t1);  // rr = 7: the block's first row
-                        }
-                        if (rr == 0) acc[blk - 1] = max_lo16(acc[blk - 1], ev);
-                        else evb = ev;
-                    }
-                }
-            };
-            // the pairing term of cell (i, 8g) (partner X(i+1, 8g-1)) is a
-            // candidate for Q(i, 8g): it joins the closure at split point 8g
-            // as one more term, formed before Q arrives
-            // (X(i, j) >= 0, so 0 stands for no candidate)
-            int pt = 0;
-            if (i < T - 1) pt = (int)((gmask >> i) & 1u) + xl + u0p;
-            // closure over j' in [8g, 8g+8), then across the 8 lane groups:
-            // packed 16-bit adds and maxima over the pairs, then the two
-            // halves and the pairing candidate (the row step is bound by
-            // instruction issue on its SIMD as much as by its chain, so
-            // fewer instructions win here over a shallower 32-bit tree)
-            // (with 32-bit values, a tree of 3-input maxima)
-            int xc;
-            if constexpr (kPacked) {
-                typedef short s16x2 __attribute__((ext_vector_type(2)));
-                const s16x2 a0 = __builtin_bit_cast(s16x2, qa.x) + __builtin_bit_cast(s16x2, up[0]);
-                const s16x2 a1 = __builtin_bit_cast(s16x2, qa.y) + __builtin_bit_cast(s16x2, up[1]);
-                const s16x2 a2 = __builtin_bit_cast(s16x2, qa.z) + __builtin_bit_cast(s16x2, up[2]);
-                const s16x2 a3 = __builtin_bit_cast(s16x2, qa.w) + __builtin_bit_cast(s16x2, up[3]);
-                const s16x2 mm = __builtin_elementwise_max(__builtin_elementwise_max(a0, a1),
-                                                           __builtin_elementwise_max(a2, a3));
-                xc = max(max((int)mm.x, (int)mm.y), pt);
-            } else {
-                const int m0 = max(max(qa.x + ureg[0], qa.y + ureg[1]), qa.z + ureg[2]);
-                const int m1 = max(max(qa.w + ureg[3], qb.x + ureg[4]), qb.y + ureg[5]);
-                const int m2 = max(max(qb.z + ureg[6], qb.w + ureg[7]), pt);
-                xc = max(max(m0, m1), m2);
-            }
-            const int xi = max_over_groups(xc);  // X(i, j)
-            __builtin_amdgcn_sched_barrier(0);
-            // pushes of row i: into row 8*blk+g (one split; -inf unless the row
-            // is above i), or for other q into every row above
-            if constexpr (kBlockFR) {
-                acc[blk] = max(acc[blk], lp[blk] + xi);
-            } else {
-#pragma unroll
-                for (int b = 0; b <= blk; ++b) acc[b] = max(acc[b], lp[b] + xi);
-            }
-            // the last row of a block: the next row (in block blk-1) takes
-            // its Q from acc[blk-1] now, so its end-tile terms go in first.
-            // The lean form sums them here at every row: it is bound by
-            // instruction issue, not by the row's chain, which the default
-            // form keeps them off by summing after the writes below
-            if (kLean || rr == 0) edge_terms();
-            if constexpr (kBlockFR) {
-                if (rr == 0 && blk >= 1) {
-                    // block blk finished: its q-groups into every row above it
-#pragma unroll
-                    for (int gg = 0; gg < GPB; ++gg) {
-                        const int k = blk * GPB + gg;
-                        const int top = k * Q;
-                        // column word of group k at column j from rows top..top+q-1
-                        int xs[Q];
-#pragma unroll
-                        for (int p2 = 0; p2 < Q; ++p2) xs[p2] = (top + p2 == i) ? xi : Xs[(top + p2) * 64 + j];
-                        uint32_t cbits = 0;
-                        if constexpr (Q == 8) {
-                            cbits = drop_bits8(xs);
-                        } else {
-#pragma unroll
-                            for (int p2 = 1; p2 <= M; ++p2) cbits |= (uint32_t)(xs[p2 - 1] > xs[p2]) << (p2 - 1);
-                        }
-                        const uint32_t cw = (cbits << 16) | (uint32_t)xs[0];
-                        const uint4 wa = *reinterpret_cast<const uint4*>(&LW[k * 64 + 8 * g]);
-                        const uint4 wb = *reinterpret_cast<const uint4*>(&LW[k * 64 + 8 * g + 4]);
-                        const uint32_t ws[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
-#pragma unroll
-                        for (int b = 0; b < blk; ++b) acc[b] = max_lo16(acc[b], rterm(Rl, ws[b], cw));
-                    }
-                }
-            }
-            // Q of row i-1 for this lane's column (pairing partner X(i, j-1)
-            // is the lane to the left; column 8w gets it from its readers)
-            if (i >= 1) {
-                // row_shr:1.  Lanes with c = 0 take no left partner, so what
-                // they read does not matter (lanes 0, 16, 32, 48 read 0)
-                const int left = __builtin_amdgcn_mov_dpp(xi, 0x111, 0xF, 0xF, true);
-                const int bo = (i - 1) >> 3;
-                // every lane writes its own row's candidate: slot (i-1) & 7
-                // holds row i-1's
-                Qs[(i - 1) & 1][g][j] = (QCell)max(acc[bo], left + pb);
-            }
-            // (the 8 lanes of a column hold the same X; all of them store
-            // it, so that the store is not masked)
-            Xs[i * 64 + j] = (Cell)xi;
-            if (!kLean && rr > 0) edge_terms();
-            if constexpr (kStageEdges) {
-#pragma unroll
-                for (int m = 0; m < kEPer; ++m) {
-                    erw[m] = ern[m];
-                    if constexpr (kLean) erc[m] = ecn[m];
-                }
-            }
-            __syncthreads();
-        }
-    }
-
-    // ---- emit: dense cells, row words (ballot), column words
-    int xcol[8];  // X(8 * wave + r, lane)
+    const unsigned long long cm = ((unsigned long long)s.cm[1][lane] << 32) | s.cm[0][lane];
+    const int top = s.top[lane];
     {
-        const int wv = wave, ln = lane;  // row-major view: wave -> 8 rows, lane -> column
-        int xv[8], xlft[8];  // every LDS read first: X(i, ln) and X(i, ln-1)
+        const int r0 = 8 * wave;
+        const uint32_t cm8 = (uint32_t)(cm >> r0);
+        int v = top + __popcll((cm >> r0) >> 8);  // X(r0 + 8, lane)
+        unsigned long long H = __ballot(v > __shfl_up(v, 1));  // horizontal differences (column 0's is not used)
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int i = wv * 8 + r;
-            xv[r] = Xs[i * 64 + ln];
-            xlft[r] = Xs[i * 64 + max(ln - 1, 0)];
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) xcol[r] = xv[r];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int i = wv * 8 + r;
-            const int v = xv[r];
-            if (i < T) {
-                if (ln < T) (Fw + (long long)(aT + i) * ld + bT)[(unsigned)ln] = (int16_t)v;
-                const unsigned long long diff = __ballot(ln > 0 && ln < T && v > xlft[r]);
-                if (ln < T && (ln % Q) == 0) {
-                    uint32_t h = 0;
-                    if constexpr (M > 0) h = (uint32_t)(diff >> (ln + 1)) & ((1u << M) - 1u);
-                    RSw[(ln / Q) * 64 + i] = ((h << M) << 16) | (uint32_t)v;
+        for (int r = 7; r >= 0; --r) {
+            const int i = r0 + r;
+            const uint32_t bit = (cm8 >> r) & 1u;
+            const unsigned long long dl = __ballot(bit);
+            v += (int)bit;
+            H ^= dl ^ (dl << 1);
+            if (T == 64 || i < T) {
+                if (T == 64 || lane < T) (Fw + (long long)(aT + i) * ld + bT)[(unsigned)lane] = (int16_t)v;
+                if ((T == 64 || lane < T) && (lane % Q) == 0) {
+                    uint32_t hb = 0;
+                    if constexpr (M > 0) hb = (uint32_t)((H >> lane) >> 1) & ((1u << M) - 1u);
+                    RSw[(lane / Q) * 64 + i] = ((hb << M) << 16) | (uint32_t)v;
                 }
-            } else if (ln < G) {
+            } else if (lane < G) {
                 // padding row (T < 64): readers load whole 64-row lines, so
                 // give it words that keep their sums bounded and R in range
-                RSw[ln * 64 + i] = 0;
+                RSw[lane * 64 + i] = 0;
             }
         }
     }
-    if constexpr (Q == 8) {
-        // q = 8: group k = wave holds rows 8k..8k+7, this lane's xv[], so
-        // the column word of (group wave, column lane) needs no LDS reads
-        CSw[wave * 64 + lane] = (drop_bits8(xcol) << 16) | (uint32_t)(uint16_t)xcol[0];
-    } else
-    for (int e = tid; e < G * 64; e += kTileThreads) {
-        const int k = e >> 6, jj = e & 63;
-        if (jj < T) {
-            const int top = k * Q;
-            uint32_t cbits = 0;
-#pragma unroll
-            for (int p = 1; p <= M; ++p)
-                cbits |= (uint32_t)(Xs[(top + p - 1) * 64 + jj] > Xs[(top + p) * 64 + jj]) << (p - 1);
-            CSw[k * 64 + jj] = (cbits << 16) | (uint32_t)(uint16_t)Xs[top * 64 + jj];
-        } else {
-            CSw[k * 64 + jj] = 0;  // padding column, as for padding rows
-        }
+    for (int k = wave; k < G; k += kTileThreads / 64) {
+        const unsigned long long u = cm >> (k * Q);  // the group's rows are its low bits
+        uint32_t cw = 0;  // padding column, as for padding rows
+        if (T == 64 || lane < T)
+            cw = (((uint32_t)u & ((1u << M) - 1u)) << 16) | (uint32_t)(top + __popcll(u));
+        CSw[k * 64 + lane] = cw;
     }
 }
 
@@ -1041,8 +723,8 @@ void k_tile(const TileWork* __restrict__ items, const uint8_t* __restrict__ Rg)
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
-    __shared__ __align__(16) TileLds<Q, kWide> s;
-    tile_body<Q, true, kWide>(items[blockIdx.x], Rl, Rg, s, [] {}, [] {});
+    __shared__ __align__(16) TileLds<Q> s;
+    tile_body<Q>(items[blockIdx.x], Rl, Rg, s);
 }
 
 // One wavefront step in one launch: workgroups [0, ntile) finish the tiles
@@ -1065,17 +747,17 @@ void k_stage(const TileWork* __restrict__ titems, int ntile,
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
-    __shared__ __align__(16) TileLds<Q, kWide> s;
+    __shared__ __align__(16) TileLds<Q> s;
     const int b = blockIdx.x;
     if (b < ntile) {
-        tile_body<Q, true, kWide>(titems[b], Rl, Rg, s, [] {}, [] {});
+        tile_body<Q>(titems[b], Rl, Rg, s);
     } else {
         load_R<RSZ>(Rl, Rg, kTileThreads);
         __syncthreads();
         const BetweenWork& it = bitems[b - ntile];
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         between_body<Q, 16, kTileThreads / 64 / 4>(it, Rl, it.f.RS, it.f.CS, wave, threadIdx.x & 63,
-                                                   reinterpret_cast<uint16_t*>(s.Xs));
+                                                   &s.P[0][0][0]);
     }
 }
 
