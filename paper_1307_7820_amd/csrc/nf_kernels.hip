@@ -62,6 +62,18 @@ __device__ __forceinline__ uint32_t r_index_s(uint32_t rw, uint32_t cw)
     return idx;
 }
 
+// The same with both words in vector registers.
+__device__ __forceinline__ uint32_t r_index_v(uint32_t rw, uint32_t cw)
+{
+    uint32_t idx;
+    __asm__("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:WORD_1"
+            : "=v"(idx)
+            : "v"(rw), "v"(cw));
+    return idx;
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // max of the low 16 bits of a, b and c as unsigned numbers, one VALU
 // instruction (the high halves of the operands are ignored).
 __device__ __forceinline__ uint32_t max3_u16(uint32_t a, uint32_t b, uint32_t c)
@@ -73,23 +85,29 @@ __device__ __forceinline__ uint32_t max3_u16(uint32_t a, uint32_t b, uint32_t c)
 
 // Copy the q-dependent R table (RSZ bytes) into LDS.  From 1 KB on by DMA
 // (global -> LDS, no registers and no LDS store; a wave moves 1 KB and RSZ is
-// a multiple of it, so no lane reads past R or writes past Rl), waited for
-// here; below that through registers.  The caller's barrier follows.
+// a multiple of it, so no lane reads past R or writes past Rl), which the
+// caller waits for (vector memory counter); below that through registers.
+// The caller's barrier follows.
 template <int RSZ>
-__device__ __forceinline__ void load_R(uint8_t* Rl, const uint8_t* __restrict__ Rg, int nthr)
+__device__ __forceinline__ void issue_R(uint8_t* Rl, const uint8_t* __restrict__ Rg, int nthr)
 {
     if constexpr (RSZ >= 1024) {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
         for (int base = wave * 1024; base < RSZ; base += nthr * 16)  // wave-uniform
             __builtin_amdgcn_global_load_lds((const NF_GLOBAL void*)(Rg + base + lane * 16),
                                              (__attribute__((address_space(3))) void*)(Rl + base), 16, 0, 0);
-        __builtin_amdgcn_s_waitcnt(0);
     } else if constexpr (RSZ >= 16) {
         for (int x = threadIdx.x * 16; x < RSZ; x += nthr * 16)
             *reinterpret_cast<uint4*>(Rl + x) = *reinterpret_cast<const uint4*>(Rg + x);
     } else {
         if (threadIdx.x < RSZ) Rl[threadIdx.x] = Rg[threadIdx.x];
     }
+}
+template <int RSZ>
+__device__ __forceinline__ void load_R(uint8_t* Rl, const uint8_t* __restrict__ Rg, int nthr)
+{
+    issue_R<RSZ>(Rl, Rg, nthr);
+    if constexpr (RSZ >= 1024) __builtin_amdgcn_s_waitcnt(0);
 }
 
 // Between-group maxima for the RPW rows r0..r0+RPW-1 (wave-uniform) and column j
@@ -239,27 +257,46 @@ __device__ __forceinline__ uint32_t bits3(uint32_t a, uint32_t b, uint32_t c)
 }
 constexpr int kA = 0xF0, kB = 0xCC, kC = 0xAA;  // the three operands in a table
 
-// Slacks of 32 split points (one per bit) in one lane.
+// Slacks of 32 split points (one per bit) in one lane.  A row's change (+ 1 at
+// the bits of c where up is all ones, - 1 where it is 0) is taken in two
+// parts: mark() moves the set of zero slacks, which the next row waits for,
+// and ripple() the words, which it does not.  A block of at most four rows
+// that starts with every slack below 12 needs the four low words only: no
+// slack passes 15 or leaves 0 downwards there.
 struct Slack {
     uint32_t p[6];
-    uint32_t nz;  // the OR of p: bit b is 0 where the slack is 0
+    uint32_t zero, one;  // the split points of slack 0 and 1
 
-    __device__ __forceinline__ void test()
+    template <int kWords>
+    __device__ __forceinline__ void find_one()
     {
-        nz = bits3<kA | kB | kC>(bits3<kA | kB | kC>(p[0], p[1], p[2]), bits3<kA | kB | kC>(p[3], p[4], p[5]), 0u);
+        uint32_t hi = bits3<kA | kB | kC>(p[1], p[2], p[3]);
+        if constexpr (kWords == 6) hi = bits3<kA | kB | kC>(hi, p[4], p[5]);
+        one = p[0] & ~hi;
     }
-    // at the bits of c: + 1 where up is all ones, - 1 where it is 0
-    __device__ __forceinline__ void step(uint32_t c, uint32_t up)
+    __device__ __forceinline__ void begin()
+    {
+        zero = ~(bits3<kA | kB | kC>(p[0], p[1], p[2]) | bits3<kA | kB | kC>(p[3], p[4], p[5]));
+        find_one<6>();
+    }
+    __device__ __forceinline__ void mark(uint32_t c, uint32_t up)
+    {
+        zero = bits3<(kA & kB) | (~kA & kC)>(c, one & ~up, zero);
+    }
+    template <int kWords>
+    __device__ __forceinline__ void ripple(uint32_t c, uint32_t up)
     {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
+        for (int k = 0; k < kWords - 1; ++k) {
             const uint32_t carry = bits3<kA & ~(kB ^ kC)>(c, p[k], up);
             p[k] ^= c;
             c = carry;
         }
-        p[5] ^= c;
-        test();
+        p[kWords - 1] ^= c;
+        find_one<kWords>();
     }
+    // nonzero at the slacks of 12 and more
+    __device__ __forceinline__ uint32_t large() const { return bits3<kA | (kB & kC)>(p[4], p[3], p[2]) | p[5]; }
 };
 
 // bit `pos` of x as a mask (all ones or 0), one instruction
@@ -276,12 +313,12 @@ __device__ __forceinline__ uint32_t with_lane(uint32_t old, uint32_t v)
     return old;
 }
 
-// f(7), f(6), ..., f(0), each with its number as a constant
-template <int r = 7, class F>
-__device__ __forceinline__ void rows8(F&& f)
+// f(r), f(r-1), ..., f(0), each with its number as a constant
+template <int r, class F>
+__device__ __forceinline__ void rows_down(F&& f)
 {
     f(std::integral_constant<int, r>{});
-    if constexpr (r > 0) rows8<r - 1>(f);
+    if constexpr (r > 0) rows_down<r - 1>(f);
 }
 
 // For each of the 64 rows of a lane's code (S_{a+1} of row `lane`), the rows
@@ -351,27 +388,31 @@ __device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int ti
         Slack lo{}, hi{};
         lo.p[5] = ~vlo;  // never 0 at split points that are not left of j
         hi.p[5] = ~vhi;
-        lo.test();
-        hi.test();
+        lo.begin();
+        hi.begin();
         unsigned long long cm = 0;
         for (int b = 7; b >= 0; --b) {
             const uint32_t pmb = (uint32_t)(pm >> (8 * b));
             const unsigned long long pts = ~((256ull << (8 * b)) - 1);  // the split points of the blocks below
             uint32_t rlo = 0, rhi = 0;  // lane r: dL(8b + r, .)
-            rows8([&](auto rc) {
+            rows_down<7>([&](auto rc) {
                 constexpr int r = rc;
                 if (T < 64 && 8 * b + r >= T) return;
                 const uint32_t pb = bit_mask(pmb, r);
                 const unsigned long long st =
-                    __ballot(((bits3<~kA & kB>(lo.nz, blo, 0u) | bits3<~kA & kB>(hi.nz, bhi, 0u)) & pb) != 0);
+                    __ballot((bits3<(kA & kB) | kC>(lo.zero, blo, hi.zero & bhi) & pb) != 0);
                 const unsigned long long cl =
-                    __ballot((bits3<~kA & kB>(lo.nz, (uint32_t)st, 0u) | bits3<~kA & kB>(hi.nz, (uint32_t)(st >> 32), 0u)) != 0);
+                    __ballot(bits3<(kA & kB) | kC>(lo.zero, (uint32_t)st, hi.zero & (uint32_t)(st >> 32)) != 0);
                 const unsigned long long dl = st | cl;
                 const uint32_t up = (dl >> j) & 1 ? ~0u : 0u;
                 // split points i < j' < j move; j' = i joins with slack 0
                 const unsigned long long rm = pts | ((0xffull & (0xfeull << r)) << (8 * b));
-                lo.step(bits3<(kA ^ kB) & kC>(up, (uint32_t)dl, vlo & (uint32_t)rm), up);
-                hi.step(bits3<(kA ^ kB) & kC>(up, (uint32_t)(dl >> 32), vhi & (uint32_t)(rm >> 32)), up);
+                const uint32_t cl_lo = bits3<(kA ^ kB) & kC>(up, (uint32_t)dl, vlo & (uint32_t)rm);
+                const uint32_t cl_hi = bits3<(kA ^ kB) & kC>(up, (uint32_t)(dl >> 32), vhi & (uint32_t)(rm >> 32));
+                lo.mark(cl_lo, up);
+                hi.mark(cl_hi, up);
+                lo.ripple<6>(cl_lo, up);
+                hi.ripple<6>(cl_hi, up);
                 cm = (cm << 1) | (up & 1u);
                 rlo = with_lane<r>(rlo, (uint32_t)dl);
                 rhi = with_lane<r>(rhi, (uint32_t)(dl >> 32));
@@ -466,34 +507,51 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 // Cell X(i, j) = F(AT+i, BT+j) is the maximum of P(i, j), the best split in
 // the tiles strictly between A and B (the between maxima of acc and the
 // groups of the two end tiles C = A+1, C = B-1), the pairing term, and the
-// splits inside tiles A and B.  P is computed first (8 rows per wavefront,
-// Eq. 3 lookups); the rows then go bottom-up in bits, as above: a cell rises
-// over the one below when P does, when a pairing or a split inside the tile
-// says so.  The row below row T-1 is row 0 of tile (A+1, B), finished one
-// step ago (or of the main-diagonal tile), and the slacks E carry over from
+// splits inside tiles A and B.  The rows go bottom-up in bits, as above: a
+// cell rises over the one below when P does, when a pairing or a split inside
+// the tile says so.  The row below row T-1 is row 0 of tile (A+1, B), finished
+// one step ago (or of the main-diagonal tile), and the slacks E carry over from
 // there, so no step rebuilds them; V starts empty at the tile's last row.
+// (MI355X, against the max-plus closure by all eight wavefronts: n = 6000
+// 1.90 -> 1.37 ms, 4096 folds of 50..2000 bases 16.9 -> 10.7 ms.)
 //
-// The rows are taken by four wavefronts, 16 columns each.  Lane 16h + c of
-// wavefront w holds column 16w + c and the split points 16h .. 16h+15 of both
-// kinds: E in the low half of its slack words, V in the high half, so that one
-// ripple moves both.  A wavefront works 8 rows (a block) behind its left
-// neighbour, from which it needs the rows' delta bits only; a barrier
-// separates the blocks.  (MI355X, against the max-plus closure by all eight
-// wavefronts: n = 6000 1.90 -> 1.49 ms, 4096 folds of 50..2000 bases
-// 16.9 -> 11.2 ms.)
+// The wavefronts form a pipeline over blocks of four rows, one barrier a block:
+//   waves 2, 3, 6, 7  look up the end tiles' groups of a block (Eq. 3, one row
+//               each) and write its P, two blocks ahead of wave 0.  A row is
+//               three LDS round trips, about 570 cycles; with two rows on each
+//               of two wavefronts the lookups bounded the pipeline;
+//   waves 0, 1  take the rows, columns 0..31 and 32..63: lane 32h + c of wave
+//               w holds column 32w + c and the split points 32h .. 32h+31 of
+//               both kinds.  Wave 1 needs of wave 0 only the rows' delta bits
+//               and follows two blocks behind, so that everything a block
+//               reads from LDS is loaded a block ahead and no LDS round trip
+//               sits on the rows' chain;
+//   waves 4, 5  write the finished block: dense cells and column words, row
+//               words.
+// A block of the rows is 190 instructions (about 850 cycles: a wavefront
+// issues one in four cycles, and the ballots' waits are filled); a fold of few
+// tiles a step is bound by the 16 + 3 blocks of this chain.  (MI355X: against
+// four wavefronts of 16 columns with all lookups ahead of the rows and all
+// writing behind, n = 6000 1.487 -> 1.373 ms, n = 500 119 -> 103 us, q = 5
+// n = 3001 926 -> 762 us.)
 constexpr int kTileThreads = 512;
-constexpr int kChainWaves = 4;
-static_assert(kTileThreads == 512, "the tile finish maps 8 wavefronts onto 8 row blocks");
+static_assert(kTileThreads == 512, "the tile finish assigns roles to 8 wavefronts");
 
 template <int Q>
 struct TileLds {
-    // M[h][i]: bits 31..16 = dL(i, 16h .. 16h+15); bits 15..0 = delta(i, .) of
-    // the columns 16h .. 16h+15 once finished (h = 3 first holds, in bit 15,
-    // delta of the column left of the tile, for column 0)
-    alignas(16) uint32_t M[4][64];
-    alignas(16) uint16_t P[8][64][8];  // P(i, j) at [i / 8][j][i % 8]
-    uint32_t cm[2][64];                // delta(32 u + b, j): bit b of cm[u][j]
-    int32_t top[64];                   // X(T, j): the row below row T-1
+    static constexpr int G = groups_per_tile(Q);
+    // the end tiles' words of a row fit the registers of a wavefront; for
+    // other q all of P is looked up before the rows start
+    static constexpr bool kPipe = G <= 16;
+    static constexpr int NE = 2 * G;                          // end-tile groups
+    static constexpr int kES = kPipe ? (NE + 3) / 4 * 4 + 4 : 4;  // 16-byte rows, banks spread
+    // rows of bits: [0], [1]: delta(i, .) of the columns 0..31 and 32..63 once
+    // finished; [2]: delta of the column left of the tile in bit 31; [3]: zero;
+    // [4], [5]: dL(i, .) of the split points 0..31 and 32..63; [6], [7]: the
+    // split points below row i among them
+    alignas(16) uint32_t W[8][64];
+    alignas(16) uint16_t P[16][64][4];            // P(i, j) at [i / 4][j][i % 4]
+    alignas(16) uint32_t EB[kPipe ? 64 : 1][kES];  // EB[i][e*G + k]: row word of row i, group k of end tile e
 };
 
 // max(0, P - x) of the P in the low or high half of pair, nonzero when P > x
@@ -513,18 +571,31 @@ __device__ __forceinline__ uint32_t above(uint32_t pair, uint32_t x)
     return d;
 }
 
+// A workgroup barrier for LDS alone.  __syncthreads() also waits for the
+// wavefront's global accesses, which would put the latency of the finished
+// cells' stores into every block of the pipeline.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // The finish of one tile by kTileThreads threads.  R is copied from Rg
 // (global) into Rl.
 template <int Q>
 __device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const uint8_t* __restrict__ Rg,
                                           TileLds<Q>& s)
 {
+    using Lds = TileLds<Q>;
     constexpr int M = Q - 1;
     constexpr int G = groups_per_tile(Q);
     constexpr int T = tile_size(Q);
     constexpr int SW = state_words(Q);
     constexpr int RW = row_words(Q);
     constexpr int RSZ = 1 << (2 * M);
+    constexpr int NE = Lds::kPipe ? Lds::NE : 4;
+    constexpr int NE4 = (NE + 3) / 4 * 4;
 
     const FoldDesc& f = it.f;
     const int A = it.A, d = it.d, B = A + d;
@@ -535,180 +606,318 @@ __device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const
     const int aT = A * T, bT = B * T;
     const NF_GLOBAL int16_t* F = (const NF_GLOBAL int16_t*)f.F;
     const NF_GLOBAL uint8_t* codes = (const NF_GLOBAL uint8_t*)f.codes;
-    const NF_GLOBAL uint32_t* rsA = (const NF_GLOBAL uint32_t*)f.RS + tile_index(f.NT, A, 0) * RW;
-    const NF_GLOBAL uint32_t* csA = (const NF_GLOBAL uint32_t*)f.CS + tile_index(f.NT, A, 0) * SW;
+    const NF_GLOBAL uint32_t* RSr = (const NF_GLOBAL uint32_t*)f.RS;
+    const NF_GLOBAL uint32_t* CSr = (const NF_GLOBAL uint32_t*)f.CS;
     NF_GLOBAL uint32_t* rsB = (NF_GLOBAL uint32_t*)f.RS + tile_index(f.NT, B, 0) * RW;
     NF_GLOBAL uint32_t* csB = (NF_GLOBAL uint32_t*)f.CS + tile_index(f.NT, B, 0) * SW;
+    NF_GLOBAL int32_t* acc = (NF_GLOBAL int32_t*)it.acc;
+    const bool between = it.nslot > 0;
 
-    // ---- set-up: R, the rows' bits of tile (A, A), the row below, the halo
-    load_R<RSZ>(Rl, Rg, kTileThreads);
-    if (tid < 256) {
-        const int h = wave, i = lane;
-        uint32_t m = (h < 2 ? rsA : csA)[kRowBits + i];
-        m = (h & 1) ? (m & 0xffff0000u) : (m << 16);
-        if (i >= T) m = 0;
-        if (h == 3 && i < T) {
-            // delta(i, -1); nothing lies below row T-1 left of tile (B, B)
-            const int up = F[(aT + i) * ld + bT - 1];
-            const int dn = (d == 1 && i == T - 1) ? 0 : (int)F[(aT + i + 1) * ld + bT - 1];
-            if (up > dn) m |= 1u << 15;
+    // ---- set-up.  Every global load goes out before the first LDS store of
+    // loaded data (which waits for it), so that the tile pays about one memory
+    // round trip here.
+    issue_R<RSZ>(Rl, Rg, kTileThreads);
+    constexpr int kLines = Lds::kPipe ? (NE + 7) / 8 : 1;
+    uint32_t line[kLines];  // row words of end-tile group wave + 8u, row `lane` (0 where the end tile does not exist)
+    if constexpr (Lds::kPipe) {
+#pragma unroll
+        for (int u = 0; u < kLines; ++u) {
+            const int x = wave + 8 * u;
+            const int e = x >= G ? 1 : 0, k = x - e * G;
+            line[u] = 0;
+            if (x < NE && d >= 2 + e) line[u] = (RSr + tile_index(f.NT, A, e == 0 ? 1 : d - 1) * RW + k * 64)[(unsigned)lane];
         }
-        s.M[h][i] = m;
-    } else if (wave == 4) {
-        s.top[lane] = lane < T ? (int)F[(aT + T) * ld + bT + lane] : 0;
     }
-
-    // the row wavefronts' own state
-    const int h = lane >> 4, c = lane & 15;
-    const int j = 16 * (wave & 3) + c;
-    Slack sl{};
-    uint32_t vr = 0, own = 0, left = 0;
-    unsigned long long pm = 0;
-    uint32_t x = 0;
-    if (wave < kChainWaves) {
-        typedef const NF_GLOBAL uint16_t* half_ptr;
-        // the split points of this lane left of column j
-        const uint32_t below = j >= T ? 0u : (j >= 16 * h + 16 ? 0xffffu : (j > 16 * h ? (1u << (j - 16 * h)) - 1 : 0u));
+    auto store_lines = [&] {
+        if constexpr (Lds::kPipe) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
-            sl.p[k] = ((half_ptr)(k < 3 ? rsB : csB))[(k % 3) * 256 + 4 * j + h] & below;
-        vr = below;
-        own = h == wave ? 0xffffu : 0u;
-        left = (j > 0 && ((j - 1) >> 4) == h) ? 1u << ((j - 1) & 15) : 0u;
-        pm = pair_rows(lane < T ? (int)codes[aT + lane] : 4, (int)codes[bT + j - 1]);
-        if (j >= T) pm = 0;
-        x = j < T ? (uint32_t)(int)F[(aT + T) * ld + bT + j] : 0u;
-        if (j == 0 && h == 3) {
-            // column 0: the column left of the tile is its split point -1, bit
-            // 15 here, with slack X(T, 0) - X(T, -1)
-            const int xl = d == 1 ? (int)x : (int)F[(aT + T) * ld + bT - 1];
-            sl.p[0] = ((int)x > xl) ? 1u << 15 : 0u;
-            vr = left = 1u << 15;
-        }
-        sl.p[5] |= 0xffffu & ~vr;      // never 0 where there is no split point
-        if (j >= T) sl.p[5] = ~0u;
-        sl.test();
-    }
-
-    // ---- P for the rows 8 wave .. 8 wave + 7, column `lane`
-    {
-        int acc[8];
-        const int r0 = 8 * wave;
-        NF_GLOBAL int32_t* accb = (NF_GLOBAL int32_t*)it.acc + r0 * 64;
-        if (it.nslot > 0) {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) acc[r] = (accb + r * 64)[(unsigned)lane];
-        } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) acc[r] = 0;
-        }
-        __syncthreads();  // R
-        if (d >= 2) between_accumulate<Q, 8, 1>(acc, Rl, f.RS, f.CS, f.NT, A, B, A + 1, A + 2, r0, lane, 0);
-        if (d >= 3) between_accumulate<Q, 8, 1>(acc, Rl, f.RS, f.CS, f.NT, A, B, B - 1, B, r0, lane, 0);
-        if (it.nslot > 0) {  // hand the accumulator back zeroed for its next use
-#pragma unroll
-            for (int r = 0; r < 8; ++r) (accb + r * 64)[(unsigned)lane] = 0;
-        }
-        uint4 pk = make_uint4((uint32_t)acc[0] | ((uint32_t)acc[1] << 16), (uint32_t)acc[2] | ((uint32_t)acc[3] << 16),
-                              (uint32_t)acc[4] | ((uint32_t)acc[5] << 16), (uint32_t)acc[6] | ((uint32_t)acc[7] << 16));
-        if (lane >= T) pk = make_uint4(0u, 0u, 0u, 0u);
-        *reinterpret_cast<uint4*>(&s.P[wave][lane][0]) = pk;
-    }
-    __syncthreads();
-
-    // ---- rows bottom-up, block b = 7 - (phase - wave) of 8 rows
-    uint32_t cml = 0, cmh = 0;
-    for (int phase = 0; phase < 8 + kChainWaves - 1; ++phase) {
-        const int b = 7 - (phase - wave);
-        if (wave < kChainWaves && b >= 0 && b < 8) {
-            const uint4 pk = *reinterpret_cast<const uint4*>(&s.P[b][j][0]);
-            const uint4 ma = *reinterpret_cast<const uint4*>(&s.M[h][8 * b]);
-            const uint4 mb = *reinterpret_cast<const uint4*>(&s.M[h][8 * b + 4]);
-            const uint32_t ps[4] = {pk.x, pk.y, pk.z, pk.w};
-            const uint32_t ms[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
-            const uint32_t pmb = (uint32_t)(pm >> (8 * b));
-            const uint32_t rmask = (h == (b >> 1) && j < T) ? ~0u : 0u;  // lanes that hold the split points of this block
-            uint32_t bit = 1u << (16 + (b & 1) * 8 + 7);
-            uint32_t rows = 0;  // lane r: delta(8b + r, .) of this wavefront's columns
-            uint32_t cm8 = 0;
-            rows8([&](auto rc) {
-                constexpr int r = rc;
-                if (T == 64 || 8 * b + r < T) {
-                    const uint32_t up_p = above<r & 1>(ps[r >> 1], x);
-                    const uint32_t cand = bits3<kA | (kB & kC)>(ms[r], bit_mask(pmb, r), left);
-                    const unsigned long long b1 = __ballot(bits3<(~kA & kB) | kC>(sl.nz, cand, up_p) != 0);
-                    const uint32_t t1 = (uint32_t)b1 | (uint32_t)(b1 >> 32);
-                    const uint32_t st = t1 | (t1 >> 16);
-                    const unsigned long long b2 = __ballot(bits3<~kA & kB & kC>(sl.nz, st, own) != 0);
-                    const uint32_t dl = st | (uint32_t)(b2 >> (16 * wave));
-                    const uint32_t up = bit_mask(dl, c);
-                    const uint32_t mv = bits3<kA | (kB & kC)>(ms[r], dl, own);
-                    sl.step(bits3<(kA ^ kB) & kC>(up, mv, vr), up);
-                    vr = bits3<kA | (kB & kC)>(vr, rmask, bit);
-                    x -= up;
-                    cm8 = __builtin_amdgcn_alignbit(cm8, up, 31);
-                    rows = with_lane<r>(rows, dl);
-                }
-                bit >>= 1;
-            });
-            cmh = __builtin_amdgcn_alignbit(cmh, cml, 24);
-            cml = (cml << 8) | cm8;
-            // the block's bits for the wavefronts to the right and the emit
-            if (lane < 8) reinterpret_cast<uint16_t*>(&s.M[wave][8 * b + lane])[0] = (uint16_t)rows;
-        }
-        __syncthreads();
-    }
-    if (wave < kChainWaves) {
-        if (h == 0) {
-            s.cm[0][j] = cml;
-            s.cm[1][j] = cmh;
-        }
-        typedef NF_GLOBAL uint16_t* half_out;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) ((half_out)(k < 3 ? rsB : csB))[(k % 3) * 256 + 4 * j + h] = (uint16_t)sl.p[k];
-    }
-    __syncthreads();
-
-    // ---- emit: dense cells, row words, column words; wavefront w takes the
-    // rows 8w .. 8w+7, lane = column
-    const long long t_idx = tile_index(f.NT, A, d);
-    NF_GLOBAL int16_t* Fw = (NF_GLOBAL int16_t*)f.F;
-    NF_GLOBAL uint32_t* RSw = (NF_GLOBAL uint32_t*)(f.RS + t_idx * RW);
-    NF_GLOBAL uint32_t* CSw = (NF_GLOBAL uint32_t*)(f.CS + t_idx * SW);
-    const unsigned long long cm = ((unsigned long long)s.cm[1][lane] << 32) | s.cm[0][lane];
-    const int top = s.top[lane];
-    {
-        const int r0 = 8 * wave;
-        const uint32_t cm8 = (uint32_t)(cm >> r0);
-        int v = top + __popcll((cm >> r0) >> 8);  // X(r0 + 8, lane)
-        unsigned long long H = __ballot(v > __shfl_up(v, 1));  // horizontal differences (column 0's is not used)
-#pragma unroll
-        for (int r = 7; r >= 0; --r) {
-            const int i = r0 + r;
-            const uint32_t bit = (cm8 >> r) & 1u;
-            const unsigned long long dl = __ballot(bit);
-            v += (int)bit;
-            H ^= dl ^ (dl << 1);
-            if (T == 64 || i < T) {
-                if (T == 64 || lane < T) (Fw + (long long)(aT + i) * ld + bT)[(unsigned)lane] = (int16_t)v;
-                if ((T == 64 || lane < T) && (lane % Q) == 0) {
-                    uint32_t hb = 0;
-                    if constexpr (M > 0) hb = (uint32_t)((H >> lane) >> 1) & ((1u << M) - 1u);
-                    RSw[(lane / Q) * 64 + i] = ((hb << M) << 16) | (uint32_t)v;
-                }
-            } else if (lane < G) {
-                // padding row (T < 64): readers load whole 64-row lines, so
-                // give it words that keep their sums bounded and R in range
-                RSw[lane * 64 + i] = 0;
+            for (int u = 0; u < kLines; ++u)
+                if (wave + 8 * u < NE4) s.EB[lane][wave + 8 * u] = line[u];
+            if constexpr (NE4 > 8 * kLines) {
+                if (wave < NE4 - 8 * kLines) s.EB[lane][8 * kLines + wave] = 0;
             }
         }
+    };
+    // the end of the set-up: R and the LDS stores are complete
+    auto set_up_done = [&] {
+        if constexpr (RSZ >= 1024) __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    if constexpr (!Lds::kPipe) {
+        // all of P, rows 8 wave .. 8 wave + 7
+        set_up_done();
+        int pr[8];
+        const int r0 = 8 * wave;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) pr[r] = between ? (acc + (r0 + r) * 64)[(unsigned)lane] : 0;
+        if (d >= 2) between_accumulate<Q, 8, 1>(pr, Rl, f.RS, f.CS, f.NT, A, B, A + 1, A + 2, r0, lane, 0);
+        if (d >= 3) between_accumulate<Q, 8, 1>(pr, Rl, f.RS, f.CS, f.NT, A, B, B - 1, B, r0, lane, 0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            if (between) (acc + (r0 + r) * 64)[(unsigned)lane] = 0;
+            s.P[2 * wave + (r >> 2)][lane][r & 3] = (T == 64 || lane < T) ? (uint16_t)pr[r] : (uint16_t)0;
+        }
     }
-    for (int k = wave; k < G; k += kTileThreads / 64) {
-        const unsigned long long u = cm >> (k * Q);  // the group's rows are its low bits
-        uint32_t cw = 0;  // padding column, as for padding rows
-        if (T == 64 || lane < T)
-            cw = (((uint32_t)u & ((1u << M) - 1u)) << 16) | (uint32_t)(top + __popcll(u));
-        CSw[k * 64 + lane] = cw;
+    // Phase p of the pipeline: wave 0 takes block 15 - p, wave 1 block
+    // 15 - (p - 2), the lookups run for block 15 - (p + 2), the writing for
+    // block 15 - (p - 3).  Every wavefront passes the same barriers: one after
+    // the set-up, one after the first two blocks' P, one after each phase but
+    // the last.
+    constexpr int kPhases = 19;
+    const int h = lane >> 5, c = lane & 31;
+
+    if (wave < 2) {
+        // ---- the rows
+        const int j = 32 * wave + c;
+        Slack E{}, V{};
+        uint32_t left = 0, x = 0;
+        const uint32_t* src = s.W[3];   // delta bits of the columns to the left
+        const uint32_t* dsrc = s.W[3];  // dL
+        const uint32_t* vsrc = s.W[3];  // the split points of tile A below the row
+        // the split points of this lane left of column j
+        const uint32_t below = j >= T ? 0u : (j >= 32 * h + 32 ? ~0u : (j > 32 * h ? (1u << (j - 32 * h)) - 1 : 0u));
+        uint32_t vrE = below;
+        const uint32_t own = h == wave ? ~0u : 0u, ownb = own & below;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) E.p[k] = (k < 3 ? rsB : csB)[(k % 3) * 128 + 2 * j + h] & below;
+        unsigned long long pm = pair_rows(lane < T ? (int)codes[aT + lane] : 4, (int)codes[bT + j - 1]);
+        if (j < T) {
+            if (j > 0 && ((j - 1) >> 5) == h) left = 1u << ((j - 1) & 31);
+            x = (uint32_t)(int)F[(aT + T) * ld + bT + j];
+            if (h < wave) src = s.W[0];
+            dsrc = s.W[4 + h];
+            vsrc = s.W[6 + h];
+            if (j == 0 && h == 1) {
+                // column 0: the column left of the tile is its split point -1,
+                // bit 31 here, with slack X(T, 0) - X(T, -1)
+                const int xl = d == 1 ? (int)x : (int)F[(aT + T) * ld + bT - 1];
+                E.p[0] = ((int)x > xl) ? 1u << 31 : 0u;
+                vrE = left = 1u << 31;
+                src = s.W[2];
+            }
+        } else {
+            pm = 0;
+        }
+        E.begin();
+        V.begin();
+        store_lines();
+        set_up_done();
+        lds_barrier();
+        // what a block reads from LDS, loaded at the end of the block before it
+        uint2 pw;
+        uint4 dw, sw, vw;
+        auto fetch = [&](int b) {
+            pw = *reinterpret_cast<const uint2*>(&s.P[b][j][0]);
+            dw = *reinterpret_cast<const uint4*>(dsrc + 4 * b);
+            sw = *reinterpret_cast<const uint4*>(src + 4 * b);
+            vw = *reinterpret_cast<const uint4*>(vsrc + 4 * b);
+        };
+        if (wave == 1) {  // two phases behind
+            lds_barrier();
+            lds_barrier();
+        }
+        fetch(15);
+        // One row: 40 instructions.  Its chain goes twice through a ballot
+        // (VALU to scalar and back, 16 idle cycles each); the ripples of the
+        // row before fill those.  With four words the blocks run until a slack
+        // of 12 or more shows up, and the rest of the tile with six.
+        int b = 15;
+        bool small = __ballot((E.large() | V.large()) != 0) == 0;
+        auto blocks = [&](auto words) {
+            constexpr int W = words;
+            while (b >= 0 && (W == 6 || small)) {
+                const uint32_t pmb = (uint32_t)(pm >> (4 * b));
+                uint32_t rows = 0;  // lane r: delta(4b + r, .) of this wavefront's columns
+                uint32_t cE = 0, cV = 0, up = 0;
+                const uint32_t ps[2] = {pw.x, pw.y};
+                const uint32_t ds[4] = {dw.x, dw.y, dw.z, dw.w};
+                const uint32_t ss[4] = {sw.x, sw.y, sw.z, sw.w};
+                const uint32_t vs[4] = {vw.x, vw.y, vw.z, vw.w};
+                rows_down<3>([&](auto rc) {
+                    constexpr int r = rc;
+                    if (T == 64 || 4 * b + r < T) {
+                        const uint32_t up_p = above<r & 1>(ps[r >> 1], x);
+                        const uint32_t cand = bits3<kA | (kB & kC)>(ss[r], bit_mask(pmb, r), left);
+                        const uint32_t v = bits3<(kA & kB) | kC>(V.zero, ds[r], up_p);
+                        const unsigned long long b1 = __ballot(bits3<(kA & kB) | kC>(E.zero, cand, v) != 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (r < 3) E.ripple<W>(cE, up);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const uint32_t st = (uint32_t)b1 | (uint32_t)(b1 >> 32);
+                        const unsigned long long b2 = __ballot(bits3<kA & kB & kC>(E.zero, st, ownb) != 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (r < 3) V.ripple<W>(cV, up);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const uint32_t dl = st | ((uint32_t)b2 | (uint32_t)(b2 >> 32));
+                        up = bit_mask(dl, c);
+                        cE = bits3<(kA ^ kB) & kC>(up, bits3<kA | (kB & kC)>(ss[r], dl, own), vrE);
+                        cV = bits3<(kA ^ kB) & kC>(up, ds[r], vs[r]);
+                        E.mark(cE, up);
+                        V.mark(cV, up);
+                        x -= up;
+                        rows = with_lane<r>(rows, dl);
+                    }
+                });
+                if (lane < 4) s.W[wave][4 * b + lane] = rows;
+                --b;
+                fetch(b >= 0 ? b : 0);
+                __builtin_amdgcn_sched_barrier(0);
+                E.ripple<W>(cE, up);
+                V.ripple<W>(cV, up);
+                if (W == 4) small = __ballot((E.large() | V.large()) != 0) == 0;
+                // the barrier waits for the store of W, not for the four loads
+                // behind it (LDS accesses of a wavefront complete in order)
+                __asm__ volatile("s_waitcnt lgkmcnt(4)\n\ts_barrier" ::: "memory");
+            }
+        };
+        blocks(std::integral_constant<int, 4>{});
+        blocks(std::integral_constant<int, 6>{});
+        // the slacks for the next step's tile of this column
+#pragma unroll
+        for (int k = 0; k < 6; ++k) (k < 3 ? rsB : csB)[(k % 3) * 128 + 2 * j + h] = E.p[k];
+        for (int p = 16 + 2 * wave; p < kPhases - 1; ++p) lds_barrier();
+    } else if ((wave & 2) != 0) {
+        // ---- the lookups: P of row 4b + r0, column `lane`
+        const int r0 = (wave & 1) + ((wave >> 1) & 2);
+        uint32_t cw[NE4];  // the end tiles' column words
+        uint32_t m0 = 0, m1 = 0, m2 = 0;
+        auto maximum = [&](int b) -> uint32_t {
+            return between ? (uint32_t)(acc + (4 * b + r0) * 64)[(unsigned)lane] : 0u;
+        };
+        if constexpr (Lds::kPipe) {
+#pragma unroll
+            for (int x = 0; x < NE4; ++x) {
+                const int e = x >= G ? 1 : 0, k = x - e * G;
+                cw[x] = 0;
+                if (x < NE && d >= 2 + e)
+                    cw[x] = (CSr + tile_index(f.NT, e == 0 ? A + 1 : B - 1, e == 0 ? d - 1 : 1) * SW + k * 64)[(unsigned)lane];
+            }
+            m0 = maximum(15);
+            m1 = maximum(14);
+            m2 = maximum(13);
+        }
+        auto look_up = [&](int b, uint32_t m) {
+            const uint32_t* eb = s.EB[4 * b + r0];
+            uint32_t rw[NE4], rr[NE4];
+#pragma unroll
+            for (int u = 0; u < NE4; u += 4) {
+                const uint4 w = *reinterpret_cast<const uint4*>(eb + u);
+                rw[u] = w.x;
+                rw[u + 1] = w.y;
+                rw[u + 2] = w.z;
+                rw[u + 3] = w.w;
+            }
+#pragma unroll
+            for (int u = 0; u < NE4; ++u) rr[u] = Rl[r_index_v(rw[u], cw[u])];
+            __builtin_amdgcn_sched_barrier(0);  // every gather is out before the first sum waits
+#pragma unroll
+            for (int u = 0; u < NE4; u += 2)
+                m = max3_u16(m, rw[u] + cw[u] + rr[u], rw[u + 1] + cw[u + 1] + rr[u + 1]);
+            s.P[b][lane][r0] = (T == 64 || lane < T) ? (uint16_t)m : (uint16_t)0;
+        };
+        store_lines();
+        set_up_done();
+        if constexpr (Lds::kPipe) {
+            look_up(15, m0);
+            look_up(14, m1);
+        }
+        lds_barrier();
+        m0 = m2;
+        for (int b = 13; b > 0; b -= 2) {  // (two registers in turn: one would be copied, and waited for, each time)
+            if constexpr (Lds::kPipe) {
+                m1 = maximum(b - 1);
+                look_up(b, m0);
+            }
+            lds_barrier();
+            if constexpr (Lds::kPipe) {
+                m0 = maximum(b > 1 ? b - 2 : 0);
+                look_up(b - 1, m1);
+            }
+            lds_barrier();
+        }
+        if (Lds::kPipe && between) {  // the accumulator is handed back zeroed for its next use
+#pragma unroll
+            for (int b = 0; b < 16; ++b) (acc + (4 * b + r0) * 64)[(unsigned)lane] = 0;
+        }
+        for (int p = 14; p < kPhases - 1; ++p) lds_barrier();
+    } else {
+        // ---- the tables of the rows (the rows' bits of tile (A, A), the
+        // halo), then the finished blocks' cells and words
+        const long long t_idx = tile_index(f.NT, A, d);
+        int top = lane < T ? (int)F[(aT + T) * ld + bT + lane] : 0;  // X of the row below
+        if (wave == 4) {
+            const uint32_t lo = (RSr + tile_index(f.NT, A, 0) * RW)[kRowBits + lane];
+            const uint32_t hi = (CSr + tile_index(f.NT, A, 0) * SW)[kRowBits + lane];
+            s.W[3][lane] = 0;
+            s.W[4][lane] = lane < T ? lo : 0u;
+            s.W[5][lane] = lane < T ? hi : 0u;
+        } else {
+            uint32_t m = 0;
+            if (lane < T) {
+                // nothing lies below row T-1 left of tile (B, B)
+                const int up = F[(aT + lane) * ld + bT - 1];
+                const int dn = (d == 1 && lane == T - 1) ? 0 : (int)F[(aT + lane + 1) * ld + bT - 1];
+                if (up > dn) m = 1u << 31;
+            }
+            const unsigned long long pts = ((T == 64 ? ~0ull : (1ull << T) - 1) >> lane >> 1) << lane << 1;
+            s.W[2][lane] = m;
+            s.W[6][lane] = (uint32_t)pts;
+            s.W[7][lane] = (uint32_t)(pts >> 32);
+        }
+        store_lines();
+        set_up_done();
+        for (int p = -1; p < 3; ++p) lds_barrier();
+        if (wave == 4) {
+            NF_GLOBAL int16_t* Fw = (NF_GLOBAL int16_t*)f.F;
+            NF_GLOBAL uint32_t* CSw = (NF_GLOBAL uint32_t*)(f.CS + t_idx * SW);
+            uint32_t cbits = 0;  // the rows' bits at this column, the last row in bit 0
+#pragma unroll 2
+            for (int b = 15; b >= 0; --b) {
+                const uint4 w = *reinterpret_cast<const uint4*>(&s.W[h][4 * b]);
+                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+                rows_down<3>([&](auto rc) {
+                    constexpr int r = rc;
+                    const int i = 4 * b + r;
+                    if (T == 64 || i < T) {
+                        const uint32_t bit = (ws[r] >> c) & 1u;
+                        top += (int)bit;
+                        cbits = (cbits << 1) | bit;
+                        if (T == 64 || lane < T) (Fw + (long long)(aT + i) * ld + bT)[(unsigned)lane] = (int16_t)top;
+                        // the rows of group i / Q are complete (columns >= T: all zero)
+                        if (i % Q == 0)
+                            CSw[i / Q * 64 + lane] = ((cbits & ((1u << M) - 1u)) << 16) | (uint32_t)top;
+                    }
+                });
+                if (b > 0) lds_barrier();
+            }
+        } else {
+            NF_GLOBAL uint32_t* RSw = (NF_GLOBAL uint32_t*)(f.RS + t_idx * RW);
+            unsigned long long H = __ballot(top > __shfl_up(top, 1));  // differences along the row (column 0's is not used)
+#pragma unroll 2
+            for (int b = 15; b >= 0; --b) {
+                const uint4 w = *reinterpret_cast<const uint4*>(&s.W[h][4 * b]);
+                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+                // four rows of a group's row words are 16 bytes.  Padding rows
+                // get zero words: readers load whole 64-row lines and zero
+                // keeps their sums bounded and R in range
+                uint32_t rw[4] = {0u, 0u, 0u, 0u};
+                rows_down<3>([&](auto rc) {
+                    constexpr int r = rc;
+                    if (T == 64 || 4 * b + r < T) {
+                        const unsigned long long dl =
+                            (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)ws[r], 0) |
+                            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)ws[r], 32) << 32);
+                        H ^= dl ^ (dl << 1);
+                        top += (int)((ws[r] >> c) & 1u);
+                        const uint32_t hb = (uint32_t)((H >> lane) >> 1) & ((1u << M) - 1u);
+                        rw[r] = ((hb << M) << 16) | (uint32_t)top;
+                    }
+                });
+                if (lane % Q == 0 && lane < T)
+                    *(NF_GLOBAL u32x4*)(RSw + lane / Q * 64 + 4 * b) = u32x4{rw[0], rw[1], rw[2], rw[3]};
+                if (b > 0) lds_barrier();
+            }
+        }
     }
 }
 
