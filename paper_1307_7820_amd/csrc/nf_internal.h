@@ -66,12 +66,18 @@ __host__ __device__ inline long long tile_index(int NT, int A, int d)
 }
 __host__ __device__ inline long long tile_count(int NT) { return (long long)NT * (NT + 1) / 2; }
 
+// Whether the between-group lookups at q skip the groups that the finish
+// leaves unmarked (q = 8, the default width).  The marks lie behind the column
+// blocks: for tile (A, B), at 64 * tile_index(NT, A, B - A), one byte per row,
+// bit k = group k holds a column that rises by its pairing alone in this row.
+__host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
+
 // One sequence being folded.  All pointers are device pointers.
 struct FoldDesc {
     const uint8_t* codes;  // NT*T + 64 bytes: base codes A0 C1 G2 U3, zero padding
     int16_t* F;            // ld x ld table of F(a, b), ld = NT*T
     uint32_t* RS;          // row blocks, tile_count(NT) * row_words(q)
-    uint32_t* CS;          // column blocks, tile_count(NT) * state_words(q)
+    uint32_t* CS;          // column blocks, tile_count(NT) * state_words(q), then the marks (sparse_between)
     int n, NT, ld, pad;
 };
 

@@ -203,6 +203,7 @@ Geom make_geom(int n, int q)
     g.F_bytes = up((size_t)g.ld * g.ld * sizeof(int16_t));
     g.rs_bytes = up((size_t)tile_count(g.NT) * row_words(q) * sizeof(uint32_t));
     g.cs_bytes = up((size_t)tile_count(g.NT) * state_words(q) * sizeof(uint32_t));
+    if (sparse_between(q)) g.cs_bytes += up((size_t)tile_count(g.NT) * 64);  // the marks
     g.bytes = g.codes_bytes + g.F_bytes + g.rs_bytes + g.cs_bytes;
     return g;
 }

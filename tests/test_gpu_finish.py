@@ -39,3 +39,23 @@ def test_finish_extremes(nf, n, q):
         want = oracle.fold_table(s)
         assert score == int(want[0, n - 1]), (name, n, q)
         assert np.array_equal(T, want), (name, n, q)
+
+
+@pytest.mark.parametrize("target", ["1", "37", "4096"])
+@pytest.mark.parametrize("n", [383, 1090, 1500])
+def test_sparse_between(nf, monkeypatch, n, target):
+    """The between-group lookups at q = 8 walk only the groups the finish marks:
+    few and many marked groups in a row, chunks of one to many tiles (whole
+    fours and remainders), every table against the oracle's."""
+    monkeypatch.setenv("NF_BETWEEN_TARGET", target)  # part of a workspace's key
+    for name, s in {
+        "iid": gen.iid_sequence(n, [78, n]),
+        "stems": gen.stem_sequence(n, [79, n]),
+        "repeats": ("GGGAAACCCUUU" * n)[:n],          # a third of all groups
+        "two letters": gen.iid_sequence(n, [80, n], (0.5, 0.0, 0.0, 0.5)),
+        "halves": "C" * (n // 2) + "G" * (n - n // 2),
+    }.items():
+        score, T = nf.nf_fold(s, 8, table=True)
+        want = oracle.fold_table(s)
+        assert score == int(want[0, n - 1]), (name, n, target)
+        assert np.array_equal(T, want), (name, n, target)
