@@ -254,10 +254,19 @@ int nf_fold_dev(const uint8_t* d_codes, int n, int q, int32_t* d_score, int16_t*
     if ((rc = single_plan(n, q, &p))) return rc;
     hipStream_t s = (hipStream_t)stream;
     const Geom& g = p->geom[0];
-    HIPCHK(launch_copy_codes(d_codes, n, (uint8_t*)p->h_folds[0].codes, (int)g.codes_bytes, s));
-    if ((rc = plan_enqueue(*p, s))) return rc;
-    if (d_score) HIPCHK(hipMemcpyAsync(d_score, p->d_scores.p, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    if (d_S && n > 0) HIPCHK(launch_expand(p->h_folds[0].F, g.ld, n, d_S, s));
+    const bool table = d_S && n > 0;
+    if (p->mode == kModeFused) {
+        // the main-diagonal tiles take the codes from the caller's buffer, and
+        // the score goes to the caller's from the table (with it, if it is
+        // asked for): no launches of their own for either
+        HIPCHK(launch_diag_codes(p->q, (const TileWork*)p->d_diag.p, (int)p->sc.diag.size(), d_codes, n, s));
+        if ((rc = plan_enqueue_steps(*p, s))) return rc;
+    } else {
+        HIPCHK(launch_copy_codes(d_codes, n, (uint8_t*)p->h_folds[0].codes, (int)g.codes_bytes, s));
+        if ((rc = plan_enqueue(*p, s))) return rc;
+    }
+    if (table) HIPCHK(launch_expand(p->h_folds[0].F, g.ld, n, d_S, s, d_score));
+    else if (d_score) HIPCHK(launch_scores((const FoldDesc*)p->d_folds.p, 1, d_score, s));
     return NF_OK;
 }
 

@@ -72,6 +72,20 @@ __host__ __device__ inline long long tile_count(int NT) { return (long long)NT *
 // bit k = group k holds a column that rises by its pairing alone in this row.
 __host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
 
+// Entry e of R for vectors of length q (Section 3.1): row h = e >> (q-1),
+// column c; the largest running total of v + v-bar, 0 at k = 0.
+__host__ __device__ inline uint8_t r_entry(int q, int e)
+{
+    const int m = q - 1;
+    const int h = e >> m, c = e & ((1 << m) - 1);
+    int tot = 0, best = 0;
+    for (int p = 0; p < m; ++p) {
+        tot += ((h >> p) & 1) - ((c >> p) & 1);
+        best = tot > best ? tot : best;
+    }
+    return (uint8_t)best;
+}
+
 // One sequence being folded.  All pointers are device pointers.
 struct FoldDesc {
     const uint8_t* codes;  // NT*T + 64 bytes: base codes A0 C1 G2 U3, zero padding
@@ -200,6 +214,9 @@ hipError_t launch_between(int q, const BetweenWork* items, int nitems, const uin
 // their fold's padded codes at staged + pad1, copy them into the fold's block
 // and clear the fold's 2 NT accumulator blocks at acc).
 hipError_t launch_diag_admit(int q, const TileWork* items, int nitems, const uint8_t* staged, hipStream_t s);
+// The main-diagonal tiles of one fold whose n codes are in a device buffer of
+// the caller: read from there (mod 4) and copied, padded, into the fold's block.
+hipError_t launch_diag_codes(int q, const TileWork* items, int nitems, const uint8_t* codes, int n, hipStream_t s);
 // scores[f] = F(0, n_f)
 hipError_t launch_scores(const FoldDesc* folds, int nfolds, int32_t* scores, hipStream_t s);
 // scores[folds[f].pad] = F(0, n_f)
@@ -207,7 +224,8 @@ hipError_t launch_scores_to_slots(const FoldDesc* folds, int nfolds, int32_t* sc
 // A bounded delay of about iters x 3.4 us (at most 16) on stream s: one wavefront
 // that sleeps (perturbed schedules, nf_test_set_perturb).
 hipError_t launch_delay(int iters, hipStream_t s);
-hipError_t launch_expand(const int16_t* F, int ld, int n, int16_t* S, hipStream_t s);
+// The n x n table in the output layout from F; *score = F(0, n) if score is set.
+hipError_t launch_expand(const int16_t* F, int ld, int n, int16_t* S, hipStream_t s, int32_t* score = nullptr);
 // One optimal structure of the fold whose table F (leading dimension ld) and
 // codes are given, as n dot-bracket characters in db; *status = 0 on success.
 // spill: 2 * spill_cap entries of device scratch, spill_cap >= n/2 + 1.

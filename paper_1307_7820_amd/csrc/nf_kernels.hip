@@ -202,18 +202,8 @@ __device__ __forceinline__ void between_accumulate(int (&acc)[RPW], const uint8_
 
 __global__ void k_precompute_R(int q, uint8_t* __restrict__ R)
 {
-    const int m = q - 1;
-    const int size = 1 << m;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= size * size) return;
-    const int h = e >> m;
-    const int c = e & (size - 1);
-    int tot = 0, best = 0;  // running total of v + v-bar, starting at k = 0 with 0
-    for (int p = 1; p <= m; ++p) {
-        tot += ((h >> (p - 1)) & 1) - ((c >> (p - 1)) & 1);
-        best = max(best, tot);
-    }
-    R[e] = (uint8_t)best;
+    if (e < 1 << (2 * (q - 1))) R[e] = r_entry(q, e);
 }
 
 __global__ void k_copy_codes(const uint8_t* __restrict__ src, int n, uint8_t* __restrict__ dst, int padded)
@@ -357,28 +347,36 @@ struct DiagLds {
 // fold's block and clears its two accumulator blocks (it.acc, one per
 // diagonal parity), so that admitting a fold takes no copy or fill of its
 // own.  Nothing else reads the fold's block before this launch has ended.
+//
+// Direct codes (n >= 0, with staged == null: a single fold on device codes): the n codes are read from the caller's buffer, taken mod 4,
+// and copied padded into the fold's block in the same way.
 template <int Q>
-__device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int tid, int nthr, const uint8_t* staged)
+__device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int tid, int nthr, const uint8_t* staged,
+                                          const uint8_t* codes, int n)
 {
     constexpr int T = tile_size(Q);
     const FoldDesc& f = it.f;
     const int aT = it.A * T;
     const bool admit = staged != nullptr && it.pad2 != 0;
-    const uint8_t* src = admit ? staged + it.pad1 : f.codes;
+    const bool direct = n >= 0;
+    const uint8_t* src = direct ? codes : (admit ? staged + it.pad1 : f.codes);
+    auto code = [&](int e) -> int { return direct ? (e < n ? src[e] & 3 : 0) : (int)src[e]; };
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
-    if (admit) {
+    if (admit || direct) {
         uint8_t* dst = const_cast<uint8_t*>(f.codes);
         const int hi = it.A == f.NT - 1 ? f.NT * T + 64 : aT + T;
-        for (int e = aT + tid; e < hi; e += nthr) dst[e] = src[e];
+        for (int e = aT + tid; e < hi; e += nthr) dst[e] = (uint8_t)code(e);
+    }
+    if (admit) {
         int4* a0 = reinterpret_cast<int4*>(it.acc + (size_t)it.A * kTileCells);
         int4* a1 = reinterpret_cast<int4*>(it.acc + (size_t)(f.NT + it.A) * kTileCells);
         for (int e = tid; e < kTileCells / 4; e += nthr) a0[e] = a1[e] = make_int4(0, 0, 0, 0);
     }
     if (wave == 0) {
         const int j = lane;
-        const int ca = src[aT + j];                              // S_{a+1} for a = aT + lane
-        const int cb = (aT + j - 1 >= 0) ? src[aT + j - 1] : 0;  // S_b for b = aT + j
+        const int ca = code(aT + j);                              // S_{a+1} for a = aT + lane
+        const int cb = (aT + j - 1 >= 0) ? code(aT + j - 1) : 0;  // S_b for b = aT + j
         // split points below j; pairing rows i <= j - 2
         const unsigned long long below = j < T ? (1ull << j) - 1 : 0ull;
         unsigned long long pm = pair_rows(ca, cb) & (below >> 1);
@@ -442,10 +440,11 @@ __device__ __forceinline__ void diag_body(const TileWork& it, DiagLds& s, int ti
 }
 
 template <int Q>
-__global__ __launch_bounds__(kThreads) void k_diag(const TileWork* __restrict__ items, const uint8_t* staged)
+__global__ __launch_bounds__(kThreads) void k_diag(const TileWork* __restrict__ items, const uint8_t* staged,
+                                                   const uint8_t* codes, int n)
 {
     __shared__ DiagLds s;
-    diag_body<Q>(items[blockIdx.x], s, threadIdx.x, kThreads, staged);
+    diag_body<Q>(items[blockIdx.x], s, threadIdx.x, kThreads, staged, codes, n);
 }
 
 // A workgroup barrier for LDS alone.  __syncthreads() also waits for the
@@ -1145,17 +1144,52 @@ __global__ void k_scores_to_slots(const FoldDesc* __restrict__ folds, int nfolds
     if (e < nfolds) scores[folds[e].pad] = folds[e].F[folds[e].n];
 }
 
-// S[i*n + j] = D(i+1, j+1) = F(i, j+1) for i <= j, 0 below the diagonal.
-__global__ void k_expand(const int16_t* __restrict__ F, int ld, int n, int16_t* __restrict__ S)
+// S[i*n + j] = D(i+1, j+1) = F(i, j+1) for i <= j, 0 below the diagonal, and
+// the score F(0, n) where asked for.  A thread writes 8 consecutive entries of
+// S (two rows' at a row's end): with kVec as one 16-byte store (S is 16-byte
+// aligned; a row of S need not be), the entries of F by 16-byte loads at their
+// 2-byte alignment where the 8 lie in one row.  The copy moves 2 n^2 bytes out
+// and n^2 in and is bound by memory; 2-byte stores at an 8-byte stride took
+// twice as long (MI355X, n = 16000: 335 us).
+struct __attribute__((packed, aligned(2))) Row8 {
+    int16_t v[8];
+};
+template <bool kVec>
+__global__ __launch_bounds__(256) void k_expand(const int16_t* __restrict__ F, int ld, int n,
+                                                int16_t* __restrict__ S, int32_t* __restrict__ score)
 {
-    const int i = blockIdx.y;
-    const int j0 = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    const int16_t* src = F + (long long)i * ld + 1;
-    int16_t* dst = S + (long long)i * n;
+    const uint32_t e0 = (blockIdx.x * 256u + threadIdx.x) * 8u, end = (uint32_t)n * (uint32_t)n;
+    if (score != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *score = F[n];
+    if (e0 >= end) return;
+    uint32_t i = e0 / (uint32_t)n, j = e0 - i * (uint32_t)n;
+    Row8 o;
+    if (j + 8 <= (uint32_t)n) {
+        if (j + 7 < i) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        if (j < n) dst[j] = j >= i ? src[j] : (int16_t)0;
+            for (int u = 0; u < 8; ++u) o.v[u] = 0;
+        } else {
+            // (columns j+1 .. j+8 <= n of row i: inside the table)
+            o = *reinterpret_cast<const Row8*>(F + (long long)i * ld + 1 + j);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (j + u < i) o.v[u] = 0;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            o.v[u] = (e0 + u < end && j >= i) ? F[(long long)i * ld + 1 + j] : (int16_t)0;
+            if (++j == (uint32_t)n) {
+                j = 0;
+                ++i;
+            }
+        }
+    }
+    if (kVec && e0 + 8 <= end) {
+        *reinterpret_cast<uint4*>(S + e0) = __builtin_bit_cast(uint4, o);
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (e0 + u < end) S[e0 + u] = o.v[u];
     }
 }
 
@@ -1178,7 +1212,8 @@ hipError_t launch_q(int which, const void* items, int nitems, const uint8_t* R, 
     if (nitems <= 0) return hipSuccess;
     dim3 grid(nitems);
     // (for the main-diagonal tiles R carries the staged codes of admission, or null)
-    if (which == 0) return launch_k(k_diag<Q>, grid, dim3(kThreads), s, e0, e1, (const TileWork*)items, R);
+    if (which == 0)
+        return launch_k(k_diag<Q>, grid, dim3(kThreads), s, e0, e1, (const TileWork*)items, R, (const uint8_t*)nullptr, -1);
     if (which == 1) return launch_k(k_tile<Q, false>, grid, dim3(kTileThreads), s, e0, e1, (const TileWork*)items, R);
     return launch_k(k_between<Q>, grid, dim3(kBetweenThreads), s, e0, e1, (const BetweenWork*)items, R);
 }
@@ -1220,6 +1255,31 @@ hipError_t launch_copy_codes(const uint8_t* src, int n, uint8_t* dst, int padded
 hipError_t launch_diag(int q, const TileWork* items, int nitems, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     return dispatch(q, 0, items, nitems, nullptr, s, e0, e1);
+}
+
+namespace {
+template <int Q>
+hipError_t diag_codes_q(const TileWork* items, int nitems, const uint8_t* codes, int n, hipStream_t s)
+{
+    return launch_k(k_diag<Q>, dim3(nitems), dim3(kThreads), s, nullptr, nullptr, items, (const uint8_t*)nullptr, codes, n);
+}
+}  // namespace
+
+hipError_t launch_diag_codes(int q, const TileWork* items, int nitems, const uint8_t* codes, int n, hipStream_t s)
+{
+    if (nitems <= 0) return hipSuccess;
+    switch (q) {
+    case 1: return diag_codes_q<1>(items, nitems, codes, n, s);
+    case 2: return diag_codes_q<2>(items, nitems, codes, n, s);
+    case 3: return diag_codes_q<3>(items, nitems, codes, n, s);
+    case 4: return diag_codes_q<4>(items, nitems, codes, n, s);
+    case 5: return diag_codes_q<5>(items, nitems, codes, n, s);
+    case 6: return diag_codes_q<6>(items, nitems, codes, n, s);
+    case 7: return diag_codes_q<7>(items, nitems, codes, n, s);
+    case 8: return diag_codes_q<8>(items, nitems, codes, n, s);
+    case 9: return diag_codes_q<9>(items, nitems, codes, n, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_diag_admit(int q, const TileWork* items, int nitems, const uint8_t* staged, hipStream_t s)
@@ -1284,11 +1344,15 @@ hipError_t launch_stage(int q, bool wide, const TileWork* titems, int ntile, con
     }
 }
 
-hipError_t launch_expand(const int16_t* F, int ld, int n, int16_t* S, hipStream_t s)
+hipError_t launch_expand(const int16_t* F, int ld, int n, int16_t* S, hipStream_t s, int32_t* score)
 {
     if (n <= 0) return hipSuccess;
-    dim3 grid((n + 1023) / 1024, n);
-    hipLaunchKernelGGL(k_expand, grid, dim3(256), 0, s, F, ld, n, S);
+    const uint32_t end = (uint32_t)n * (uint32_t)n;  // n <= 65534: below 2^32
+    const dim3 grid((end - 1) / 2048 + 1);
+    if (((uintptr_t)S & 15) == 0)
+        hipLaunchKernelGGL(k_expand<true>, grid, dim3(256), 0, s, F, ld, n, S, score);
+    else
+        hipLaunchKernelGGL(k_expand<false>, grid, dim3(256), 0, s, F, ld, n, S, score);
     return hipGetLastError();
 }
 

@@ -32,13 +32,29 @@ constexpr int kMaxDevices = 64;
 void* g_scratch[kMaxDevices] = {nullptr};  // device address of `scratch`, per device
 std::mutex g_scratch_mu;
 
-// Every work item of one fold, one workgroup per stage: stage 0 also writes
-// the main-diagonal items and the fold descriptor.
-__global__ void k_single_items(SingleSchedule S, FoldDesc fd, int32_t* acc, TileWork* diag, TileWork* tiles,
-                               BetweenWork* btw, FoldDesc* fd_out)
+constexpr int kPrepThreads = 256;
+
+// Everything a fold needs before its main-diagonal tiles, in one launch:
+// workgroups [0, NT) write the work items of one stage each (stage 0 also the
+// main-diagonal items and the fold descriptor), the next nzero clear the
+// accumulators (n16 16-byte pieces), the rest build R.
+__global__ __launch_bounds__(kPrepThreads) void k_prepare(SingleSchedule S, FoldDesc fd, int32_t* acc, TileWork* diag,
+                                                          TileWork* tiles, BetweenWork* btw, FoldDesc* fd_out,
+                                                          size_t n16, int nzero, int q, uint8_t* R)
 {
     const int sg = blockIdx.x;
     const int tid = threadIdx.x;
+    if (sg >= S.NT + nzero) {
+        const int e = (sg - S.NT - nzero) * kPrepThreads + tid;
+        if (e < 1 << (2 * (q - 1))) R[e] = r_entry(q, e);
+        return;
+    }
+    if (sg >= S.NT) {
+        uint4* p = (uint4*)acc;
+        for (size_t e = (size_t)(sg - S.NT) * kPrepThreads + tid; e < n16; e += (size_t)nzero * kPrepThreads)
+            p[e] = make_uint4(0u, 0u, 0u, 0u);
+        return;
+    }
     if (sg == 0) {
         if (tid == 0) *fd_out = fd;
         for (int A = tid; A < S.NT; A += blockDim.x) {
@@ -75,12 +91,6 @@ __global__ void k_single_items(SingleSchedule S, FoldDesc fd, int32_t* acc, Tile
         w.atomic = it.pad0;
         btw[off + k] = w;
     }
-}
-
-__global__ void k_zero(uint4* p, size_t n16)
-{
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n16) p[e] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -177,20 +187,20 @@ extern "C" int nf_fold_dev_noalloc(const uint8_t* d_codes, int n, int q, int32_t
     BetweenWork* btw = (BetweenWork*)(base + L.btw);
     FoldDesc* fdp = (FoldDesc*)(base + L.fd);
 
-    // R, the codes, cleared accumulators and the work lists, then the fill
-    HIPCHK(launch_precompute_R(q, R, s));
-    HIPCHK(launch_copy_codes(d_codes, n, fold, (int)g.codes_bytes, s));
+    // R, cleared accumulators and the work lists, then the fill (whose
+    // main-diagonal tiles take the codes from the caller's buffer)
     const size_t n16 = L.acc_bytes / 16;
-    hipLaunchKernelGGL(k_zero, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, (uint4*)acc, n16);
+    const int nzero = (int)std::min<size_t>(512, (n16 + 4 * kPrepThreads - 1) / (4 * kPrepThreads));
+    const int nR = ((1 << (2 * (q - 1))) + kPrepThreads - 1) / kPrepThreads;
+    hipLaunchKernelGGL(k_prepare, dim3(S.NT + nzero + nR), dim3(kPrepThreads), 0, s, S, fd, acc, diag, tiles, btw, fdp,
+                       n16, nzero, q, R);
     HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_single_items, dim3(S.NT), dim3(256), 0, s, S, fd, acc, diag, tiles, btw, fdp);
-    HIPCHK(hipGetLastError());
-    HIPCHK(launch_diag(q, diag, S.NT, s));
+    HIPCHK(launch_diag_codes(q, diag, S.NT, d_codes, n, s));
     const bool wide = stage_wide(n, q);
     for (int sg = 1; sg < S.NT; ++sg)
         HIPCHK(launch_stage(q, wide, tiles + S.finish_offset(sg), S.finishes(sg), btw + S.between_offset(sg),
                             S.between_count(sg), R, s));
-    if (d_score) HIPCHK(launch_scores(fdp, 1, d_score, s));
-    if (d_S && n > 0) HIPCHK(launch_expand(fd.F, g.ld, n, d_S, s));
+    if (d_S && n > 0) HIPCHK(launch_expand(fd.F, g.ld, n, d_S, s, d_score));
+    else if (d_score) HIPCHK(launch_scores(fdp, 1, d_score, s));
     return NF_OK;
 }

@@ -374,8 +374,10 @@ void Plan::release_graph()
 {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
-    exec = nullptr;
-    graph = nullptr;
+    if (steps_exec) (void)hipGraphExecDestroy(steps_exec);
+    if (steps_graph) (void)hipGraphDestroy(steps_graph);
+    exec = steps_exec = nullptr;
+    graph = steps_graph = nullptr;
 }
 
 static bool use_graphs()
@@ -469,22 +471,25 @@ int plan_allocate(Plan& p)
 // Fused steps: one launch per step on one stream.  Kernel order alone gives
 //     finish(s)  after between(s)  (in launch s-1)
 //     between(s+1) after finish(s-1) (launch s-1)
-static int plan_enqueue_fused(Plan& p, hipStream_t s)
+static int enqueue_fused_steps(Plan& p, hipStream_t s)
 {
     const uint8_t* R = nullptr;
     int rc = get_R(p.q, &R);
     if (rc) return rc;
     const Schedule& sc = p.sc;
-    for (int sg = 0; sg < sc.stages; ++sg) {
-        if (sg == 0) {
-            HIPCHK(launch_diag(p.q, (const TileWork*)p.d_diag.p, (int)sc.diag.size(), s));
-            if (sc.btw_cnt[0] > 0)
-                HIPCHK(launch_between(p.q, (const BetweenWork*)p.d_btw.p + sc.btw_off[0], sc.btw_cnt[0], R, s));
-        } else {
-            HIPCHK(launch_stage(p.q, p.wide, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg],
-                                (const BetweenWork*)p.d_btw.p + sc.btw_off[sg], sc.btw_cnt[sg], R, s));
-        }
-    }
+    for (int sg = 1; sg < sc.stages; ++sg)
+        HIPCHK(launch_stage(p.q, p.wide, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg],
+                            (const BetweenWork*)p.d_btw.p + sc.btw_off[sg], sc.btw_cnt[sg], R, s));
+    return NF_OK;
+}
+
+// (the between work of the first stages is empty: a tile has group tiles from
+// diagonal 4 on, which stage 3 runs)
+static int plan_enqueue_fused(Plan& p, hipStream_t s)
+{
+    HIPCHK(launch_diag(p.q, (const TileWork*)p.d_diag.p, (int)p.sc.diag.size(), s));
+    int rc = enqueue_fused_steps(p, s);
+    if (rc) return rc;
     HIPCHK(launch_scores((const FoldDesc*)p.d_folds.p, (int)p.geom.size(), (int32_t*)p.d_scores.p, s));
     return NF_OK;
 }
@@ -640,16 +645,16 @@ int plan_profile(Plan& p, hipStream_t s, int reps, nf_kernel_profile_t* out)
     return NF_OK;
 }
 
-int plan_enqueue(Plan& p, hipStream_t s)
+// Replay the graph of what `enqueue` puts on a stream, captured at the first call.
+static int replay(Plan& p, hipGraph_t& graph, hipGraphExec_t& exec, int (*enqueue)(Plan&, hipStream_t), hipStream_t s)
 {
-    if (!use_graphs()) return plan_enqueue_direct(p, s);
-    if (!p.exec) {
+    if (!exec) {
         const uint8_t* R = nullptr;
         int rc = get_R(p.q, &R);  // outside the capture
         if (rc) return rc;
         hipStream_t cs = ctx().capture_stream;
         HIPCHK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        rc = plan_enqueue_direct(p, cs);
+        rc = enqueue(p, cs);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(cs, &g);
         if (rc) {
@@ -657,15 +662,35 @@ int plan_enqueue(Plan& p, hipStream_t s)
             return rc;
         }
         if (e != hipSuccess) return fail(NF_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-        p.graph = g;
-        e = hipGraphInstantiate(&p.exec, g, nullptr, nullptr, 0);
+        graph = g;
+        e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
         if (e != hipSuccess) {
-            p.release_graph();
+            exec = nullptr;
+            (void)hipGraphDestroy(g);
+            graph = nullptr;
             return fail(NF_E_DEVICE, "graph instantiate failed: %s", hipGetErrorString(e));
         }
     }
-    HIPCHK(hipGraphLaunch(p.exec, s));
+    HIPCHK(hipGraphLaunch(exec, s));
     return NF_OK;
+}
+
+int plan_enqueue(Plan& p, hipStream_t s)
+{
+    if (!use_graphs()) return plan_enqueue_direct(p, s);
+    return replay(p, p.graph, p.exec, plan_enqueue_direct, s);
+}
+
+int plan_enqueue_steps(Plan& p, hipStream_t s)
+{
+    if (p.sc.stages <= 1) return NF_OK;
+    // a graph's launch costs the device about 6 us before its first kernel, a
+    // launch of a step costs the host about 2 us while a step takes 11: few
+    // steps go out one by one (MI355X, 7 steps 104 -> 98 us), many as a graph
+    // that leaves the host free
+    constexpr int kDirectStages = 16;
+    if (!use_graphs() || p.sc.stages <= kDirectStages) return enqueue_fused_steps(p, s);
+    return replay(p, p.steps_graph, p.steps_exec, enqueue_fused_steps, s);
 }
 
 int make_plan(const std::vector<int>& ns, int q, std::unique_ptr<Plan>& out, int target, int wide)

@@ -113,6 +113,8 @@ struct Plan {
     size_t device_bytes = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    hipGraph_t steps_graph = nullptr;  // the fused steps alone (plan_enqueue_steps)
+    hipGraphExec_t steps_exec = nullptr;
     ~Plan();
     void release_graph();
 };
@@ -164,6 +166,9 @@ TileWork to_work(const TileItem& it, const std::vector<FoldDesc>& fd, int32_t* a
 BetweenWork to_work(const BetweenItem& it, const std::vector<FoldDesc>& fd, int32_t* acc_base);
 int plan_enqueue(Plan& p, hipStream_t s);
 int plan_enqueue_direct(Plan& p, hipStream_t s);
+// The fused steps of a single fold after its main-diagonal tiles, without the
+// score: the caller launches the tiles (launch_diag_codes) and takes the score.
+int plan_enqueue_steps(Plan& p, hipStream_t s);
 int plan_mode_for(const std::vector<int>& NTs);
 // NF_BETWEEN=plain: the between-group work of new plans runs the plain
 // recurrence (k_between_plain, the ablation of the lookup) on staged steps;
