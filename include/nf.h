@@ -288,13 +288,13 @@ int nf_autotune_q(int n);
  * out of range. */
 int nf_autotune_target(int n, int q);
 /* Whether a single fold of length n at group width q (0 = what q = 0
- * resolves to) runs its fused wavefront steps in the wide shape: the same
- * kernel code held to fewer registers so that a CU takes three workgroups
- * instead of two, which speeds the between-group lookups of long folds and
- * slows each tile finish.  Only at q = 8.  The tuned choice of n's bucket
- * (fourth column of the cache file: 1 wide, 0 not) if it was tuned at this q,
- * else wide for n >= 8192; NF_STAGE_WIDE=0|1 overrides.  Returns 1 or 0, or
- * NF_E_INVAL for n or q out of range. */
+ * resolves to) runs its fused wavefront steps in the wide shape: two
+ * workgroups for each between-group chunk, with half the rows and twice the
+ * group tiles at a time, which speeds the lookups of long folds and costs
+ * short ones the extra workgroups.  Only at q = 8.  The tuned choice of n's
+ * bucket (fourth column of the cache file: 1 wide, 0 not) if it was tuned at
+ * this q, else wide for n >= 8192; NF_STAGE_WIDE=0|1 overrides.  Returns 1 or
+ * 0, or NF_E_INVAL for n or q out of range. */
 int nf_autotune_wide(int n, int q);
 /* Time the fill at length n (reps folds each, after one warm-up fold): first
  * q in qmin..qmax at the default target, then the targets 1024, 256, 512,

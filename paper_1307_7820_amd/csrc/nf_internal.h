@@ -50,12 +50,6 @@ constexpr int kRowsPerWave = 16;
 constexpr int kBetweenSplit = kBetweenThreads / 64 / (64 / kRowsPerWave);
 static_assert(kBetweenSplit == 1 || kBetweenSplit == 2, "one or two wavefronts per row block");
 constexpr int kTileCells = 64 * 64;
-// A between chunk spans at least this many group tiles C when the step's work
-// allows: a chunk has fixed costs (R into LDS, the merge of its row blocks,
-// its atomic maxima), and MI355X folds of n = 10000 and 16000 ran 0.4-0.7%
-// faster with 4 than with 1 (the smallest chunks come in the early steps).
-constexpr int kMinChunkTiles = 4;
-
 __host__ __device__ constexpr int groups_per_tile(int q) { return 64 / q; }
 __host__ __device__ constexpr int tile_size(int q) { return (64 / q) * q; }
 __host__ __device__ constexpr int state_words(int q) { return (64 / q) * 64; }  // column block
@@ -71,6 +65,15 @@ __host__ __device__ inline long long tile_count(int NT) { return (long long)NT *
 // blocks: for tile (A, B), at 64 * tile_index(NT, A, B - A), one byte per row,
 // bit k = group k holds a column that rises by its pairing alone in this row.
 __host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
+
+// A between chunk spans at least this many group tiles C when the step's work
+// allows: a chunk has fixed costs (R into LDS, the first words, its atomic
+// maxima).  With the marks a turn takes four or eight tiles and a short chunk
+// leaves it part empty (MI355X, q = 8, minimum 4, 6 and 8: n = 6000 1366, 1317
+// and 1346 us; n = 16000 7179, 7142 and 7112 us); without them a chunk's time
+// goes with its tiles, and more of them fill the chip (q = 4, n = 1283,
+// minimum 4 and 6: 293 and 312 us).
+__host__ __device__ constexpr int min_chunk_tiles(int q) { return sparse_between(q) ? 6 : 4; }
 
 // Entry e of R for vectors of length q (Section 3.1): row h = e >> (q-1),
 // column c; the largest running total of v + v-bar, 0 at k = 0.
@@ -120,6 +123,7 @@ struct TileItem {
 // A + (stage parity) * max_slots.
 struct SingleSchedule {
     int NT = 0, target = 1;
+    int min_chunk = 1;  // min_chunk_tiles(q)
 
     __host__ __device__ int max_slots() const { return NT >= 5 ? NT - 4 : 0; }
     // chunks per tile of diagonal dd (0 when the diagonal has no between work)
@@ -128,7 +132,7 @@ struct SingleSchedule {
         if (dd < 4 || NT <= dd) return 0;
         const long long W = (long long)(NT - dd) * (dd - 3);
         long long chunk = (W + target - 1) / target;
-        if (chunk < kMinChunkTiles) chunk = kMinChunkTiles;
+        if (chunk < min_chunk) chunk = min_chunk;
         return (int)((dd - 3 + chunk - 1) / chunk);
     }
     __host__ __device__ int finishes(int sg) const { return (sg >= 1 && sg < NT) ? NT - sg : 0; }
@@ -187,8 +191,8 @@ static_assert(sizeof(BetweenWork) == 80, "BetweenWork layout");
 
 // One fused wavefront step: ntile tile finishes and nbtw between chunks of
 // the next diagonal in one launch of kTileThreads-thread workgroups.  wide
-// (q = 8 only; ignored otherwise) selects the shape that fits three
-// workgroups per CU instead of two.
+// (q = 8 only; ignored otherwise) gives each chunk two workgroups with half
+// the rows each.
 hipError_t launch_stage(int q, bool wide, const TileWork* titems, int ntile, const BetweenWork* bitems, int nbtw,
                         const uint8_t* R, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // Whether a single fold of length n at q runs the wide fused step: the tuned
@@ -205,9 +209,8 @@ hipError_t launch_copy_codes(const uint8_t* src, int n, uint8_t* dst, int padded
 // With events e0/e1 the dispatch records the kernel's own start and end.
 hipError_t launch_diag(int q, const TileWork* items, int nitems, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);
-// wide (q = 8 only): the lean finish, three workgroups per CU
 hipError_t launch_tile(int q, const TileWork* items, int nitems, const uint8_t* R, hipStream_t s,
-                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, bool wide = false);
+                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_between(int q, const BetweenWork* items, int nitems, const uint8_t* R, hipStream_t s,
                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // The main-diagonal tiles of newly admitted folds (items with pad2 = 1 read

@@ -8,9 +8,10 @@
 //   * k_tile: the finish of tile (A, B): folds in the partial maxima, the
 //     groups of the two tiles next to the diagonal ends (C = A+1, C = B-1),
 //     the pairing term and the splits that fall inside tiles A and B
-//     (the "residual" split points of Section 3.1), cell by cell along the
-//     tile's own anti-diagonals; then writes the dense int16 cells and the
-//     packed row/column words.
+//     (the "residual" split points of Section 3.1), row by row from the
+//     bottom, each row held as the bits of its differences; then writes the
+//     dense int16 cells and the packed row/column words (and, at q = 8, the
+//     marks by which k_between skips groups).
 //   * k_diag: the tiles (A, A) on the main diagonal, where every split point
 //     is inside the tile.
 // Max is idempotent and order-free, so the result does not depend on how the
@@ -36,7 +37,8 @@ namespace {
 // stream write only that diagonal), and the fused step that runs it
 // (d = s+1) writes only the words of diagonal s.  Packed blocks of different
 // tiles never share a cache line (each block is a multiple of 256 bytes).
-// The tile finish reads every packed word through vector loads.
+// A tile finish at q < 4 reads the end tiles' row words this way too, also of
+// earlier diagonals only.
 #define NF_GLOBAL __attribute__((address_space(1)))
 #define NF_CONST __attribute__((address_space(4)))
 template <class T>
@@ -510,92 +512,127 @@ __device__ __forceinline__ void between_body(const BetweenWork& it, const uint8_
 // are left, on repeats at most a third.  The maxima over them are not the
 // maxima over all groups, but every cell comes out the same.
 //
-// Eight wavefronts, 8 rows each, lane = column, four group tiles C at a time:
-// their column words go to LDS, a wavefront's row words into registers by
-// row (lane 32 (r & 1) + 8q + k of word r / 2 holds row r, tile q, group k),
-// and each row's marks into a scalar word whose set bits are walked in
-// batches of four lookups: the lane read of the row word, the column word's
-// address, the R index, the sum, half a max: 4.5 VALU instructions against
-// 2.5 for a group of the dense walk, on a fifth of the groups.  (MI355X, dense
-// -> sparse: n = 16000 11.17 -> 8.18 ms, 4096 folds 10.74 -> 9.19 ms, n = 6000
-// 1.369 -> 1.329 ms; marking costs the rows 6 instructions each, n = 500
-// 103 -> 109 us.)
-template <int Q>
+// Lane = column; kH tells how an item is cut.  kH = 1: one workgroup, eight
+// rows a wavefront, four group tiles C at a time.  kH = 2 (the wide shape of
+// the fused step): two workgroups with 32 rows each, four rows a wavefront,
+// eight tiles at a time.  The tiles' column words go to LDS, a wavefront's row
+// words into registers by row (lane 8q + k of word r holds row r, tile q,
+// group k), and each row's marks into a scalar word whose set bits are walked
+// in batches: the lane read of the row word, the column word's address, the R
+// index, the sum, half a max: 4.5 VALU instructions against 2.5 for a group of
+// the dense walk, on a fifth of the groups.  A batch is two dependent LDS
+// round trips (about 350 cycles), so few and full batches count: with kH = 2 a
+// row has 11 marks a turn against 5 to 6, which serves long items (MI355X,
+// n = 16000 7.69 -> 7.16 ms); short ones lose with twice the workgroups (4096
+// folds of 50..2000 bases 9.11 -> 9.62 ms).
+template <int Q, int kH>
 struct SparseLds {
-    static constexpr int kRowStride = 40;  // words; the transposed stores hit every bank once
-    alignas(16) uint32_t col[32 * 64];     // column word of group 8q + k, column j
-    uint32_t row[8][8 * kRowStride];       // per wavefront: row word of row r, group 8q + k
+    alignas(16) uint32_t col[32 * kH * 64];  // column word of group 8q + k, column j
+    // per wavefront: row word of row r, group g at [r][g ^ swizzle(r)] (the
+    // transposed stores hit every bank once)
+    alignas(16) uint32_t row[8][256];
 };
 
-template <int Q>
-__device__ __forceinline__ void between_sparse(const BetweenWork& it, uint8_t* Rl, const uint8_t* __restrict__ Rg,
-                                               SparseLds<Q>& s)
+template <int Q, int kH>
+__device__ __forceinline__ void between_sparse(const BetweenWork& it, int half, uint8_t* Rl,
+                                               const uint8_t* __restrict__ Rg, SparseLds<Q, kH>& s)
 {
-    static_assert(Q == 8, "eight groups a tile, 64 posts");
+    static_assert(Q == 8 && (kH == 1 || kH == 2), "eight groups a tile, 64 posts");
     constexpr int RSZ = 1 << (2 * (Q - 1));
     constexpr int SW = state_words(Q);
     constexpr int RW = row_words(Q);
-    constexpr int RS = SparseLds<Q>::kRowStride;
+    constexpr int NR = 8 / kH;   // rows a wavefront
+    constexpr int NC = 4 * kH;   // tiles at a time
+    constexpr int NG = 32 * kH;  // their groups
+    using Marks = typename std::conditional<kH == 2, unsigned long long, uint32_t>::type;
+    auto swizzle = [](int r) { return kH == 2 ? 16 * r : 8 * (r >> 1); };
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int NT = it.f.NT, A = it.A, B = A + it.d, c1 = it.c1;
-    const int r0 = 8 * wave;
-    const NF_GLOBAL uint32_t* RSr = (const NF_GLOBAL uint32_t*)it.f.RS;
-    const NF_GLOBAL uint32_t* CSr = (const NF_GLOBAL uint32_t*)it.f.CS;
-    const NF_GLOBAL uint8_t* LV = (const NF_GLOBAL uint8_t*)(it.f.CS + tile_count(NT) * SW);
+    const int r0 = 32 * half + NR * wave;
+    const NF_GLOBAL char* RSr = (const NF_GLOBAL char*)it.f.RS;
+    const NF_GLOBAL char* CSr = (const NF_GLOBAL char*)it.f.CS;
+    const NF_GLOBAL char* LV = (const NF_GLOBAL char*)(it.f.CS + tile_count(NT) * SW);
     issue_R<RSZ>(Rl, Rg, kBetweenThreads);
 
-    // the words of the tiles C .. C+3 (zero from c1 on)
-    u32x4 colw;
+    // The words of the tiles C .. C+NC-1.  Tile numbers and byte offsets fit 32
+    // bits (at most 524800 blocks of 2 KB), so an address is the fold's base, a
+    // scalar offset and a lane's.  From c1 on nothing is loaded: no mark uses it.
+    static_assert(SW == 512 && RW == 512, "2 KB blocks");
+    auto index = [&](int a, int d) { return (uint32_t)(d * NT - d * (d - 1) / 2 + a); };
+    auto lane_index = [&](int d) { return (uint32_t)(__mul24(d, NT) - (__mul24(d, d - 1) >> 1) + A); };  // of (A, A+d)
+    // a row word's lane: tile kH p + rq, row rr, group lane & 7; a mark's: tile mq, row mr
+    const int rq = kH == 2 ? lane >> 5 : 0, rr0 = (lane >> 3) & (NR - 1);
+    const uint32_t roff = (uint32_t)((lane & 7) * 64 + r0 + rr0) * 4u;
+    const int mq = lane & (NC - 1);
+    const uint32_t moff = (uint32_t)(r0 + ((lane / NC) & (NR - 1)));
+    u32x4 colw[kH];
     uint32_t roww[4], mark;
-    const int ct = __builtin_amdgcn_readfirstlane(tid >> 7);  // two wavefronts stage the column words of tile C + ct
     auto load = [&](int C) {
-        colw = u32x4{0u, 0u, 0u, 0u};
-        if (C + ct < c1)
-            colw = *(const NF_GLOBAL u32x4*)(CSr + tile_index(NT, C + ct, B - C - ct) * SW + 4 * (tid & 127));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            roww[q] = 0;
-            if (C + q < c1) roww[q] = (RSr + tile_index(NT, A, C + q - A) * RW + r0)[(unsigned)((lane & 7) * 64 + (lane >> 3))];
+        for (int i = 0; i < kH; ++i) {
+            const int id = kH * wave + i;  // half a tile's column words
+            const int cc = C + (id >> 1);
+            if (cc < c1)
+                colw[i] = *(const NF_GLOBAL u32x4*)(CSr + (index(cc, B - cc) * 2048u + (uint32_t)(id & 1) * 1024u +
+                                                           (uint32_t)lane * 16u));
         }
-        // lane 4r + q: the marks of row r0 + r, tile C + q
-        const int q = lane & 3;
-        mark = 0;
-        if (lane < 32 && C + q < c1) mark = LV[tile_index(NT, A, C + q - A) * 64 + r0 + (lane >> 2)];
-    };
-    uint32_t acc[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) acc[r] = 0;
+        for (int p = 0; p < 4; ++p) {
+            const int d = min(C + kH * p + rq, c1 - 1) - A;
+            if (C + kH * p < c1)
+                roww[p] = *(const NF_GLOBAL uint32_t*)(RSr + ((kH == 2 ? lane_index(d) : index(A, d)) * 2048u + roff));
+        }
+        mark = *(const NF_GLOBAL uint8_t*)(LV + (lane_index(min(C + mq, c1 - 1) - A) * 64u + moff));
+    };
+    uint32_t acc[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[r] = 0;
+#pragma unroll
+    for (int i = 0; i < kH; ++i) colw[i] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int p = 0; p < 4; ++p) roww[p] = 0;
     load(it.c0);
     __builtin_amdgcn_s_waitcnt(0);  // the R transfer (and the first words)
-    for (int C = it.c0; C < c1; C += 4) {
+    for (int C = it.c0; C < c1; C += NC) {
         __syncthreads();  // the lookups of the tiles before are done
-        *reinterpret_cast<u32x4*>(&s.col[4 * tid]) = colw;
+#pragma unroll
+        for (int i = 0; i < kH; ++i) *reinterpret_cast<u32x4*>(&s.col[(kH * wave + i) * 256 + 4 * lane]) = colw[i];
         uint32_t* rowl = s.row[wave];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) rowl[(lane >> 3) * RS + 8 * q + (lane & 7)] = roww[q];
-        uint32_t m4 = mark << (8 * (lane & 3));
+        for (int p = 0; p < 4; ++p) rowl[rr0 * NG + (((kH * p + rq) * 8 + (lane & 7)) ^ swizzle(rr0))] = roww[p];
+        uint32_t m4 = C + mq < c1 ? mark << (8 * (mq & 3)) : 0u;
         m4 |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m4, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
         m4 |= (uint32_t)__builtin_amdgcn_mov_dpp((int)m4, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
-        uint32_t marks[8];
+        Marks marks[NR];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) marks[r] = (uint32_t)__builtin_amdgcn_readlane((int)m4, 4 * r);
-        if (C + 4 < c1) load(C + 4);
+        for (int r = 0; r < NR; ++r) {
+            marks[r] = (uint32_t)__builtin_amdgcn_readlane((int)m4, NC * r);
+            if constexpr (kH == 2)
+                marks[r] |= (Marks)(uint32_t)__builtin_amdgcn_readlane((int)m4, NC * r + 4) << 32;
+        }
+        if (C + NC < c1) load(C + NC);
         lds_barrier();
-        uint32_t vr[4];
+        uint32_t vr[NR];  // lane g: row word of row r, group g
 #pragma unroll
-        for (int p = 0; p < 4; ++p) vr[p] = rowl[(2 * p + (lane >> 5)) * RS + (lane & 31)];
+        for (int r = 0; r < NR; ++r) vr[r] = rowl[r * NG + ((lane & (NG - 1)) ^ swizzle(r))];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            uint32_t m = marks[r];
+        for (int r = 0; r < NR; ++r) {
+            Marks m = marks[r];
             auto take = [&](auto cnt) {
                 constexpr int N = cnt;
                 uint32_t rw[N], cw[N], rr[N];
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
-                    const int g = __builtin_ctz(m);
-                    m &= m - 1;
-                    rw[u] = (uint32_t)__builtin_amdgcn_readlane((int)vr[r >> 1], g + 32 * (r & 1));
+                    int g;
+                    if constexpr (kH == 2) {
+                        g = __builtin_ctzll(m);
+                        __asm__("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(g));
+                    } else {
+                        g = __builtin_ctz(m);
+                        __asm__("s_bitset0_b32 %0, %1" : "+s"(m) : "s"(g));
+                    }
+                    rw[u] = (uint32_t)__builtin_amdgcn_readlane((int)vr[r], g);
                     cw[u] = s.col[g * 64 + lane];
                 }
 #pragma unroll
@@ -607,15 +644,19 @@ __device__ __forceinline__ void between_sparse(const BetweenWork& it, uint8_t* R
                     acc[r] = max3_u16(acc[r], t0, t1);
                 }
             };
-            int n = __builtin_popcount(m);
-            for (; n >= 4; n -= 4) take(std::integral_constant<int, 4>{});
+            constexpr int kMost = 4 * kH;
+            int n = kH == 2 ? __builtin_popcountll(m) : __builtin_popcount((uint32_t)m);
+            for (; n >= kMost; n -= kMost) take(std::integral_constant<int, kMost>{});
+            if constexpr (kH == 2) {
+                if (n & 4) take(std::integral_constant<int, 4>{});
+            }
             if (n & 2) take(std::integral_constant<int, 2>{});
             if (n & 1) take(std::integral_constant<int, 1>{});
         }
     }
     int32_t* out = it.acc + r0 * 64 + lane;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
+    for (int r = 0; r < NR; ++r) {
         const int v = (int)(acc[r] & 0xffffu);
         if (it.atomic) atomicMax(out + r * 64, v);  // several items share the tile's accumulator
         else out[r * 64] = v;
@@ -628,11 +669,11 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
-    const BetweenWork& it = items[blockIdx.x];
     if constexpr (sparse_between(Q)) {
-        __shared__ SparseLds<Q> s;
-        between_sparse<Q>(it, Rl, Rg, s);
+        __shared__ SparseLds<Q, 1> s;
+        between_sparse<Q, 1>(items[blockIdx.x], 0, Rl, Rg, s);
     } else {
+        const BetweenWork& it = items[blockIdx.x];
         __shared__ uint16_t red[kBetweenSplit == 2 ? 64 * 64 : 1];
         load_R<RSZ>(Rl, Rg, kBetweenThreads);
         __syncthreads();
@@ -1070,14 +1111,9 @@ __device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const
     }
 }
 
-template <int Q, bool kWide>
-constexpr int kStageWavesPerSimd = (Q == 8 && kWide) ? 6 : 1;
-
-// Tile finishes alone (staged steps).  kWide: the lean finish at six
-// wavefronts per SIMD, three workgroups per CU (q = 8), as in the fused step.
-template <int Q, bool kWide>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(kStageWavesPerSimd<Q, kWide>)))
-void k_tile(const TileWork* __restrict__ items, const uint8_t* __restrict__ Rg)
+// Tile finishes alone (staged steps).
+template <int Q>
+__global__ __launch_bounds__(kTileThreads) void k_tile(const TileWork* __restrict__ items, const uint8_t* __restrict__ Rg)
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
@@ -1087,19 +1123,10 @@ void k_tile(const TileWork* __restrict__ items, const uint8_t* __restrict__ Rg)
 
 // One wavefront step in one launch: workgroups [0, ntile) finish the tiles
 // of diagonal s, the rest run the between chunks of diagonal s+1 (which only
-// read diagonals <= s-1 and write the other half of the accumulators).
-//
-// Two shapes of the same code.  The default leaves the register count to the
-// compiler (two workgroups per CU at q = 8: the finish's registers and LDS
-// bound it), which keeps the finish, the fold's critical path, fastest.  The
-// wide shape (q = 8 only) holds each workgroup to 80 VGPRs (the compiler
-// spills a few registers to scratch) so that a CU takes three, six
-// wavefronts per SIMD: the between chunks, which bound long folds, then run
-// faster while each finish runs slower.  (Measured on MI355X: n = 16000
-// 13.2 -> 12.2 ms, n = 6000 2.21 -> 2.34 ms.)
-template <int Q, bool kWide>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(kStageWavesPerSimd<Q, kWide>)))
-void k_stage(const TileWork* __restrict__ titems, int ntile,
+// read diagonals <= s-1 and write the other half of the accumulators), one
+// workgroup each, or two in the wide shape (q = 8: kH of between_sparse).
+template <int Q, int kH>
+__global__ __launch_bounds__(kTileThreads) void k_stage(const TileWork* __restrict__ titems, int ntile,
                                                         const BetweenWork* __restrict__ bitems,
                                                         const uint8_t* __restrict__ Rg)
 {
@@ -1109,12 +1136,12 @@ void k_stage(const TileWork* __restrict__ titems, int ntile,
     if constexpr (sparse_between(Q)) {
         __shared__ union Lds {
             TileLds<Q> tile;
-            SparseLds<Q> between;
+            SparseLds<Q, kH> between;
         } s;
         if (b < ntile)
             tile_body<Q>(titems[b], Rl, Rg, s.tile);
         else
-            between_sparse<Q>(bitems[b - ntile], Rl, Rg, s.between);
+            between_sparse<Q, kH>(bitems[(b - ntile) / kH], (b - ntile) % kH, Rl, Rg, s.between);
     } else {
         __shared__ __align__(16) TileLds<Q> s;
         if (b < ntile) {
@@ -1214,7 +1241,7 @@ hipError_t launch_q(int which, const void* items, int nitems, const uint8_t* R, 
     // (for the main-diagonal tiles R carries the staged codes of admission, or null)
     if (which == 0)
         return launch_k(k_diag<Q>, grid, dim3(kThreads), s, e0, e1, (const TileWork*)items, R, (const uint8_t*)nullptr, -1);
-    if (which == 1) return launch_k(k_tile<Q, false>, grid, dim3(kTileThreads), s, e0, e1, (const TileWork*)items, R);
+    if (which == 1) return launch_k(k_tile<Q>, grid, dim3(kTileThreads), s, e0, e1, (const TileWork*)items, R);
     return launch_k(k_between<Q>, grid, dim3(kBetweenThreads), s, e0, e1, (const BetweenWork*)items, R);
 }
 
@@ -1288,10 +1315,8 @@ hipError_t launch_diag_admit(int q, const TileWork* items, int nitems, const uin
 }
 
 hipError_t launch_tile(int q, const TileWork* items, int nitems, const uint8_t* R, hipStream_t s, hipEvent_t e0,
-                       hipEvent_t e1, bool wide)
+                       hipEvent_t e1)
 {
-    if (wide && q == 8 && nitems > 0)
-        return launch_k(k_tile<8, true>, dim3(nitems), dim3(kTileThreads), s, e0, e1, items, R);
     return dispatch(q, 1, items, nitems, R, s, e0, e1);
 }
 
@@ -1320,7 +1345,7 @@ template <int Q>
 hipError_t stage_q(const TileWork* t, int nt, const BetweenWork* b, int nb, const uint8_t* R, hipStream_t s,
                    hipEvent_t e0, hipEvent_t e1)
 {
-    return launch_k(k_stage<Q, false>, dim3(nt + nb), dim3(kTileThreads), s, e0, e1, t, nt, b, R);
+    return launch_k(k_stage<Q, 1>, dim3(nt + nb), dim3(kTileThreads), s, e0, e1, t, nt, b, R);
 }
 }  // namespace
 
@@ -1329,7 +1354,7 @@ hipError_t launch_stage(int q, bool wide, const TileWork* titems, int ntile, con
 {
     if (ntile + nbtw <= 0) return hipSuccess;
     if (wide && q == 8)
-        return launch_k(k_stage<8, true>, dim3(ntile + nbtw), dim3(kTileThreads), s, e0, e1, titems, ntile, bitems, R);
+        return launch_k(k_stage<8, 2>, dim3(ntile + 2 * nbtw), dim3(kTileThreads), s, e0, e1, titems, ntile, bitems, R);
     switch (q) {
     case 1: return stage_q<1>(titems, ntile, bitems, nbtw, R, s, e0, e1);
     case 2: return stage_q<2>(titems, ntile, bitems, nbtw, R, s, e0, e1);

@@ -157,6 +157,7 @@ extern "C" int nf_fold_dev_noalloc(const uint8_t* d_codes, int n, int q, int32_t
     SingleSchedule S;
     S.NT = g.NT;
     S.target = between_target(n, q);
+    S.min_chunk = min_chunk_tiles(q);
     const Layout L = layout(g, S, q);
     if (L.total > (size_t)NF_NOALLOC_SCRATCH_BYTES)
         return fail(NF_E_NOMEM,

@@ -246,7 +246,7 @@ bool stage_wide(int n_single, int q)
 // tile owns one accumulator slot (numbered from *next_slot); when a tile is
 // split its chunks combine there with atomic max, otherwise the single item
 // stores.  The tile finish reads the slot and clears it for its next use.
-void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, int target,
+void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, int target, int min_chunk,
                     std::vector<BetweenItem>& out, int* next_slot,
                     std::vector<std::vector<std::pair<int, int>>>& pending)
 {
@@ -255,7 +255,7 @@ void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, in
     for (auto& fn : folds_nt)
         if (fn.second > dd) W += (long long)(fn.second - dd) * (dd - 3);
     if (W == 0) return;
-    const long long chunk = std::max<long long>(kMinChunkTiles, (W + target - 1) / target);
+    const long long chunk = std::max<long long>(min_chunk, (W + target - 1) / target);
     const int nC = dd - 3;
     const int ns = (int)((nC + chunk - 1) / chunk);
     for (auto& fn : folds_nt) {
@@ -281,7 +281,7 @@ void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, in
     }
 }
 
-void build_schedule(const std::vector<int>& NTs, int target, Schedule& sc)
+void build_schedule(const std::vector<int>& NTs, int target, int min_chunk, Schedule& sc)
 {
     const int nf = (int)NTs.size();
     int stages = 0;
@@ -322,7 +322,7 @@ void build_schedule(const std::vector<int>& NTs, int target, Schedule& sc)
         }
         sc.btw_off[sg] = (int)sc.btw.size();
         int local = 0;
-        append_between(folds_nt, sg + 1, target, sc.btw, &local, pending);
+        append_between(folds_nt, sg + 1, target, min_chunk, sc.btw, &local, pending);
         sc.btw_cnt[sg] = (int)sc.btw.size() - sc.btw_off[sg];
         for (int k = 0; k < sc.btw_cnt[sg]; ++k) btw_stage.push_back(sg);
         max_slots = std::max(max_slots, local);
@@ -517,8 +517,7 @@ int plan_enqueue_direct(Plan& p, hipStream_t s)
             HIPCHK(hipEventRecord(ev_tile, s));         // marks finish(sg-1) done
             HIPCHK(launch_delay(delay_tile, s));
             if (sc.tile_cnt[sg] > 0)
-                HIPCHK(launch_tile(p.q, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg], R, s,
-                                   nullptr, nullptr, p.tile_wide));
+                HIPCHK(launch_tile(p.q, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg], R, s));
         }
         HIPCHK(hipStreamWaitEvent(s2, ev_tile, 0));  // finish(sg-1) done
         HIPCHK(launch_delay(delay_btw, s2));
@@ -619,7 +618,7 @@ int plan_profile(Plan& p, hipStream_t s, int reps, nf_kernel_profile_t* out)
                 }
                 if (sg >= 1 && sc.tile_cnt[sg] > 0) {
                     if (!pair(a, b)) return fail(NF_E_DEVICE, "event creation failed");
-                    HIPCHK(launch_tile(p.q, tw, sc.tile_cnt[sg], R, s, a, b, p.tile_wide));
+                    HIPCHK(launch_tile(p.q, tw, sc.tile_cnt[sg], R, s, a, b));
                     recs.push_back({1, a, b, tile_lk[sg], tile_sp[sg], tile_cells[sg]});
                 }
                 if (sc.btw_cnt[sg] > 0) {
@@ -707,12 +706,7 @@ int make_plan(const std::vector<int>& ns, int q, std::unique_ptr<Plan>& out, int
     if (p->plain) p->mode = kModeStaged;  // the fused step has the lookup built in
     p->target = target > 0 ? target : between_target(ns.size() == 1 ? ns[0] : -1, q);
     p->wide = ns.size() == 1 && q == 8 && (wide >= 0 ? wide > 0 : stage_wide(ns[0], q));
-    // staged finishes in the lean shape at q = 8: three per CU (MI355X, the
-    // 4096-fold batch 20.35 -> 19.1 ms; staged single folds unchanged);
-    // NF_TILE_WIDE=0 keeps the default shape
-    p->tile_wide = q == 8;
-    if (const char* e = getenv("NF_TILE_WIDE")) p->tile_wide = q == 8 && atoi(e) != 0;
-    build_schedule(NTs, p->target, p->sc);
+    build_schedule(NTs, p->target, min_chunk_tiles(q), p->sc);
     if ((p->perturb = perturb_seed())) perturb_schedule(p->sc, p->perturb);
     int rc = plan_allocate(*p);
     if (rc) return rc;
@@ -930,10 +924,10 @@ namespace {
 
 // Check the invariants of build_schedule for folds of NT[f] tiles per side;
 // "" when they hold, else the first violation.
-std::string check_schedule(const std::vector<int>& NTs, int target)
+std::string check_schedule(const std::vector<int>& NTs, int target, int min_chunk)
 {
     Schedule sc;
-    build_schedule(NTs, target, sc);
+    build_schedule(NTs, target, min_chunk, sc);
     if (perturb_seed()) perturb_schedule(sc, perturb_seed());  // the invariants hold in any item order
     char buf[256];
     auto bad = [&](const char* fmt, long long a, long long b, long long c) {
@@ -1026,13 +1020,14 @@ std::string check_schedule(const std::vector<int>& NTs, int target)
 // The closed form SingleSchedule, which the allocation-free entry point
 // evaluates on the device, against build_schedule for one fold: the same
 // items in the same order, and the same slot count.
-std::string check_single_schedule(int NT, int target)
+std::string check_single_schedule(int NT, int target, int min_chunk)
 {
     Schedule sc;
-    build_schedule({NT}, target, sc);
+    build_schedule({NT}, target, min_chunk, sc);
     SingleSchedule S;
     S.NT = NT;
     S.target = target;
+    S.min_chunk = min_chunk;
     char buf[256];
     auto bad = [&](const char* what, int sg, long long k) {
         snprintf(buf, sizeof buf, "single schedule NT %d target %d: %s at stage %d item %lld", NT, target, what, sg, k);
@@ -1070,8 +1065,12 @@ extern "C" int nf_test_schedule(const int* NTs, int count, int target, char* msg
     std::vector<int> v(NTs, NTs + count);
     for (int x : v)
         if (x < 1) return NF_E_INVAL;
-    std::string err = nf::check_schedule(v, target);
-    if (err.empty() && count == 1 && !nf::perturb_seed()) err = nf::check_single_schedule(v[0], target);
+    std::string err;
+    for (int q : {4, 8}) {  // both minimum chunk sizes
+        const int m = nf::min_chunk_tiles(q);
+        if (err.empty()) err = nf::check_schedule(v, target, m);
+        if (err.empty() && count == 1 && !nf::perturb_seed()) err = nf::check_single_schedule(v[0], target, m);
+    }
     if (msg && cap > 0) snprintf(msg, (size_t)cap, "%s", err.c_str());
     return err.empty() ? NF_OK : 1;
 }

@@ -101,9 +101,8 @@ struct Plan {
     int mode = kModeStaged;
     bool plain = false;  // between-group work by the plain recurrence (NF_BETWEEN=plain)
     int target = 0;      // between chunks per wavefront step the schedule was built for
-    bool wide = false;   // fused steps in the wide shape (three workgroups per CU at q = 8)
+    bool wide = false;   // fused steps in the wide shape (two workgroups a between chunk at q = 8)
     unsigned perturb = 0;  // test: seed of the shuffled item order and staged delays (0: none)
-    bool tile_wide = false;  // staged finishes in the lean shape (three workgroups per CU at q = 8)
     std::vector<Geom> geom;
     std::vector<FoldDesc> h_folds;
     Schedule sc;
@@ -156,10 +155,10 @@ int resolve_q(int q, int n);
 unsigned& perturb_seed();
 void perturb_schedule(Schedule& sc, unsigned seed);
 Geom make_geom(int n, int q);
-void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, int target,
+void append_between(const std::vector<std::pair<int, int>>& folds_nt, int dd, int target, int min_chunk,
                     std::vector<BetweenItem>& out, int* next_slot,
                     std::vector<std::vector<std::pair<int, int>>>& pending);
-void build_schedule(const std::vector<int>& NTs, int target, Schedule& sc);
+void build_schedule(const std::vector<int>& NTs, int target, int min_chunk, Schedule& sc);
 int between_target(int n_single, int q);
 int plan_allocate(Plan& p);
 TileWork to_work(const TileItem& it, const std::vector<FoldDesc>& fd, int32_t* acc_base);

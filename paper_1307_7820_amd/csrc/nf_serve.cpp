@@ -582,7 +582,7 @@ void engine_main()
                 hipError_t he;
                 if (which == 0) he = launch_diag_admit(q, (const TileWork*)dptr + b, (int)(e - b), (const uint8_t*)dv, st);
                 else if (which == 1)
-                    he = launch_tile(q, (const TileWork*)dptr + b, (int)(e - b), D.R[q], st, nullptr, nullptr, true);
+                    he = launch_tile(q, (const TileWork*)dptr + b, (int)(e - b), D.R[q], st);
                 else he = launch_between(q, (const BetweenWork*)dptr + b, (int)(e - b), D.R[q], st);
                 ok = he == hipSuccess;
                 b = e;
