@@ -714,10 +714,22 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 // four wavefronts of 16 columns with all lookups ahead of the rows and all
 // writing behind, n = 6000 1.487 -> 1.373 ms, n = 500 119 -> 103 us, q = 5
 // n = 3001 926 -> 762 us.)
+//
+// Staged steps hold hundreds to thousands of finishes, four to a CU, and are
+// bound by the VALU (77% busy) and not by this chain.  There, at q = 8, the
+// lookup wavefronts walk the marked groups as between_sparse does (kWalk): 8
+// LDS reads and 18 VALU instructions for up to four groups against 20 and 40
+// for all sixteen; and every other workgroup gives the rows to wavefronts 2 and
+// 3, so that the rows, the longest role, do not all sit on the first two SIMDs
+// (workgroups go to the 8 XCDs in turn, and there to its CUs, so the parity is
+// that of the bits above the third).  4096 folds of 50..2000 bases: 9.20 ->
+// 9.07 ms by the roles, -> 8.78 ms with the walk.  A fused step keeps the
+// plain lookups: rows of many marks take two or three rounds there, longer than
+// a block of the rows (n = 3300, planted stems: 680 against 708 us).
 constexpr int kTileThreads = 512;
 static_assert(kTileThreads == 512, "the tile finish assigns roles to 8 wavefronts");
 
-template <int Q>
+template <int Q, bool kWalk>
 struct TileLds {
     static constexpr int G = groups_per_tile(Q);
     // the end tiles' words of a row fit the registers of a wavefront; for
@@ -735,6 +747,7 @@ struct TileLds {
     uint32_t K[kSparse ? 2 : 1][kSparse ? 64 : 1];  // the columns of row i that rise by their pairing alone
     alignas(16) uint16_t P[16][64][4];            // P(i, j) at [i / 4][j][i % 4]
     alignas(16) uint32_t EB[kPipe ? 64 : 1][kES];  // EB[i][e*G + k]: row word of row i, group k of end tile e
+    uint32_t CW[kWalk ? NE + 1 : 1][kWalk ? 64 : 1];  // end-tile column words [e*G + k][column], then zeros
 };
 
 // max(0, P - x) of the P in the low or high half of pair, nonzero when P > x
@@ -755,12 +768,13 @@ __device__ __forceinline__ uint32_t above(uint32_t pair, uint32_t x)
 }
 
 // The finish of one tile by kTileThreads threads.  R is copied from Rg
-// (global) into Rl.
-template <int Q>
-__device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const uint8_t* __restrict__ Rg,
-                                          TileLds<Q>& s)
+// (global) into Rl.  kWalk: the lookup wavefronts walk the marked groups only.
+// flip (0 or 1): the roles of wavefronts w and w ^ 2 change places.
+template <int Q, bool kWalk>
+__device__ __forceinline__ void tile_body(const TileWork& it, int flip, uint8_t* Rl, const uint8_t* __restrict__ Rg,
+                                          TileLds<Q, kWalk>& s)
 {
-    using Lds = TileLds<Q>;
+    using Lds = TileLds<Q, kWalk>;
     constexpr int M = Q - 1;
     constexpr int G = groups_per_tile(Q);
     constexpr int T = tile_size(Q);
@@ -773,7 +787,7 @@ __device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const
     const FoldDesc& f = it.f;
     const int A = it.A, d = it.d, B = A + d;
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) ^ (2 * flip));
     const int lane = tid & 63;
     const long long ld = f.ld;
     const int aT = A * T, bT = B * T;
@@ -962,45 +976,86 @@ __device__ __forceinline__ void tile_body(const TileWork& it, uint8_t* Rl, const
     } else if ((wave & 2) != 0) {
         // ---- the lookups: P of row 4b + r0, column `lane`
         const int r0 = (wave & 1) + ((wave >> 1) & 2);
-        uint32_t cw[NE4];  // the end tiles' column words
+        // the end tiles' column words (kWalk: this wavefront's share, for LDS);
+        // group x = e*G + k is of tile (A+1, B) or (B-1, B)
+        constexpr int kCW = kWalk ? NE4 / 4 : NE4;
+        uint32_t cw[kCW];
+        uint32_t marks = 0;  // kWalk: the marked groups of row `lane`
+        uint32_t words = 0;  // kWalk: row word of group `lane` of the row to come
         uint32_t m0 = 0, m1 = 0, m2 = 0;
         auto maximum = [&](int b) -> uint32_t {
             return between ? (uint32_t)(acc + (4 * b + r0) * 64)[(unsigned)lane] : 0u;
         };
         if constexpr (Lds::kPipe) {
 #pragma unroll
-            for (int x = 0; x < NE4; ++x) {
+            for (int u = 0; u < kCW; ++u) {
+                const int x = kWalk ? kCW * r0 + u : u;
                 const int e = x >= G ? 1 : 0, k = x - e * G;
-                cw[x] = 0;
+                cw[u] = 0;
                 if (x < NE && d >= 2 + e)
-                    cw[x] = (CSr + tile_index(f.NT, e == 0 ? A + 1 : B - 1, e == 0 ? d - 1 : 1) * SW + k * 64)[(unsigned)lane];
+                    cw[u] = (CSr + tile_index(f.NT, e == 0 ? A + 1 : B - 1, e == 0 ? d - 1 : 1) * SW + k * 64)[(unsigned)lane];
+            }
+            if constexpr (kWalk) {
+                const NF_GLOBAL uint8_t* LV = (const NF_GLOBAL uint8_t*)(CSr + tile_count(f.NT) * SW);
+                const uint32_t k0 = d >= 2 ? (LV + tile_index(f.NT, A, 1) * 64)[(unsigned)lane] : 0u;
+                const uint32_t k1 = d >= 3 ? (LV + tile_index(f.NT, A, d - 1) * 64)[(unsigned)lane] : 0u;
+                marks = k0 | (k1 << G);
             }
             m0 = maximum(15);
             m1 = maximum(14);
             m2 = maximum(13);
         }
+        [[maybe_unused]] auto fetch_words = [&](int b) { words = s.EB[4 * b + r0][lane < NE ? lane : NE]; };
         auto look_up = [&](int b, uint32_t m) {
-            const uint32_t* eb = s.EB[4 * b + r0];
-            uint32_t rw[NE4], rr[NE4];
+            if constexpr (kWalk) {
+                uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)marks, 4 * b + r0);
+                while (left != 0) {
+                    uint32_t rw[4], w[4], rr[4];
 #pragma unroll
-            for (int u = 0; u < NE4; u += 4) {
-                const uint4 w = *reinterpret_cast<const uint4*>(eb + u);
-                rw[u] = w.x;
-                rw[u + 1] = w.y;
-                rw[u + 2] = w.z;
-                rw[u + 3] = w.w;
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t x = (uint32_t)__builtin_ctz(left | (1u << NE));  // NE: the zero words
+                        left &= ~(1u << x);
+                        rw[u] = (uint32_t)__builtin_amdgcn_readlane((int)words, (int)x);
+                        w[u] = s.CW[x][lane];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) rr[u] = Rl[r_index_s(rw[u], w[u])];
+#pragma unroll
+                    for (int u = 0; u < 4; u += 2)
+                        m = max3_u16(m, rw[u] + w[u] + rr[u], rw[u + 1] + w[u + 1] + rr[u + 1]);
+                }
+                s.P[b][lane][r0] = (uint16_t)m;
+                if (b > 0) fetch_words(b - 1);
+            } else {
+                const uint32_t* eb = s.EB[4 * b + r0];
+                uint32_t rw[NE4], rr[NE4];
+#pragma unroll
+                for (int u = 0; u < NE4; u += 4) {
+                    const uint4 w = *reinterpret_cast<const uint4*>(eb + u);
+                    rw[u] = w.x;
+                    rw[u + 1] = w.y;
+                    rw[u + 2] = w.z;
+                    rw[u + 3] = w.w;
+                }
+#pragma unroll
+                for (int u = 0; u < NE4; ++u) rr[u] = Rl[r_index_v(rw[u], cw[u])];
+                __builtin_amdgcn_sched_barrier(0);  // every gather is out before the first sum waits
+#pragma unroll
+                for (int u = 0; u < NE4; u += 2)
+                    m = max3_u16(m, rw[u] + cw[u] + rr[u], rw[u + 1] + cw[u + 1] + rr[u + 1]);
+                s.P[b][lane][r0] = (T == 64 || lane < T) ? (uint16_t)m : (uint16_t)0;
             }
-#pragma unroll
-            for (int u = 0; u < NE4; ++u) rr[u] = Rl[r_index_v(rw[u], cw[u])];
-            __builtin_amdgcn_sched_barrier(0);  // every gather is out before the first sum waits
-#pragma unroll
-            for (int u = 0; u < NE4; u += 2)
-                m = max3_u16(m, rw[u] + cw[u] + rr[u], rw[u + 1] + cw[u + 1] + rr[u + 1]);
-            s.P[b][lane][r0] = (T == 64 || lane < T) ? (uint16_t)m : (uint16_t)0;
         };
+        if constexpr (kWalk) {
+#pragma unroll
+            for (int x = 0; x < kCW; ++x) s.CW[kCW * r0 + x][lane] = cw[x];
+            if (r0 == 0) s.CW[NE][lane] = 0;
+            if (r0 == 1) s.EB[lane][NE] = 0;
+        }
         store_lines();
         set_up_done();
         if constexpr (Lds::kPipe) {
+            if constexpr (kWalk) fetch_words(15);
             look_up(15, m0);
             look_up(14, m1);
         }
@@ -1117,8 +1172,9 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(const TileWork* __restric
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
-    __shared__ __align__(16) TileLds<Q> s;
-    tile_body<Q>(items[blockIdx.x], Rl, Rg, s);
+    constexpr bool kWalk = sparse_between(Q);
+    __shared__ __align__(16) TileLds<Q, kWalk> s;
+    tile_body<Q, kWalk>(items[blockIdx.x], __builtin_popcount(blockIdx.x >> 3) & 1, Rl, Rg, s);
 }
 
 // One wavefront step in one launch: workgroups [0, ntile) finish the tiles
@@ -1135,17 +1191,17 @@ __global__ __launch_bounds__(kTileThreads) void k_stage(const TileWork* __restri
     const int b = blockIdx.x;
     if constexpr (sparse_between(Q)) {
         __shared__ union Lds {
-            TileLds<Q> tile;
+            TileLds<Q, false> tile;
             SparseLds<Q, kH> between;
         } s;
         if (b < ntile)
-            tile_body<Q>(titems[b], Rl, Rg, s.tile);
+            tile_body<Q, false>(titems[b], 0, Rl, Rg, s.tile);
         else
             between_sparse<Q, kH>(bitems[(b - ntile) / kH], (b - ntile) % kH, Rl, Rg, s.between);
     } else {
-        __shared__ __align__(16) TileLds<Q> s;
+        __shared__ __align__(16) TileLds<Q, false> s;
         if (b < ntile) {
-            tile_body<Q>(titems[b], Rl, Rg, s);
+            tile_body<Q, false>(titems[b], 0, Rl, Rg, s);
         } else {
             load_R<RSZ>(Rl, Rg, kTileThreads);
             __syncthreads();

@@ -59,3 +59,19 @@ def test_sparse_between(nf, monkeypatch, n, target):
         want = oracle.fold_table(s)
         assert score == int(want[0, n - 1]), (name, n, target)
         assert np.array_equal(T, want), (name, n, target)
+
+
+@pytest.mark.parametrize("n", [127, 128, 192, 449, 1090])
+def test_walked_end_tiles(nf, monkeypatch, n):
+    """Staged steps at q = 8 look up only the marked groups of the end tiles:
+    no end tile, one and two (the first three diagonals), rows with none to all
+    of their groups marked, the last row block, every table against the
+    oracle's.  Several folds in one step, so that the wavefronts' roles are
+    taken both ways."""
+    monkeypatch.setenv("NF_MODE", "staged")  # part of a workspace's key
+    seqs = list(_patterns(n).values()) + [("GGGAAACCCUUU" * n)[:n], gen.iid_sequence(n, [81, n])]
+    scores, tables = nf.nf_fold_batch(seqs, q=8, tables=True)
+    for k, s in enumerate(seqs):
+        want = oracle.fold_table(s)
+        assert scores[k] == int(want[0, n - 1]), (k, n)
+        assert np.array_equal(tables[k], want), (k, n)
