@@ -136,7 +136,11 @@ def lds_ceiling(nf, q: int):
 def roofline_times(lookups: float, terms: float, cells_out: float, seconds: float, lds_rate: float):
     """t* = max(t_VALU, t_LDS, t_HBM) for the given algorithmic work, and the
     roofline object with the binding unit's achieved and peak rates (so that
-    frac = achieved / peak = t* / t)."""
+    frac = achieved / peak = t* / t).  The work is that of the method with
+    every group looked up.  At q = 8 the kernels skip the groups whose splits
+    cannot change a cell (four in five on these workloads), so achieved is the
+    rate at which that work is dealt with, not the issue rate of the VALU, and
+    frac can pass 1; the SQ counters under profiles/ give how busy the units are."""
     t_valu = (OPS_PER_LOOKUP * lookups + OPS_PER_TERM * terms) / PEAK_VALU_LANE_OPS
     t_lds = lookups / lds_rate
     hbm_bytes = HBM_BYTES_PER_LOOKUP * lookups + 2.0 * cells_out
@@ -160,8 +164,8 @@ def roofline(nf, codes, n, q, lds, reps=3):
     """Roofline of the kernel that takes most of the fill's device time.
 
     Algorithmic work per launch, from the work lists (nf_profile_fold):
-    3 VALU lane-ops per Eq. 3 lookup and 2 per Eq. 1 term evaluated one by
-    one, one LDS byte gather per lookup, and 6/64 HBM bytes per lookup plus
+    3 VALU lane-ops per Eq. 3 lookup, skipped ones included, and half of one
+    per Eq. 1 term inside a tile, one LDS byte gather per lookup, and 6/64 HBM bytes per lookup plus
     2 bytes per table cell written.  Duration = the kernel's own start and
     end, recorded into HIP events by its dispatch on the launching stream.
     The LDS rate is the measured row-pattern gather ceiling."""
@@ -192,8 +196,8 @@ def roofline(nf, codes, n, q, lds, reps=3):
 
 
 def fold_work(n: int, q: int):
-    """Algorithmic work of one fill, counted as the kernels run it (the same
-    counts nf_profile_fold reports per launch, summed): Eq. 3 lookups, Eq. 1
+    """Algorithmic work of one fill, in the split the kernels make of it (the
+    same counts nf_profile_fold reports per launch, summed): Eq. 3 lookups, Eq. 1
     terms evaluated one by one, and table cells written."""
     G = 64 // q
     T = G * q
