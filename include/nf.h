@@ -315,7 +315,7 @@ int nf_autotune(int n, int qmin, int qmax, int reps);
  * execution its workspace uses (see nf_fold).  For every class:
  * lookups[k] counts the Four-Russians steps of Eq. 3 on table cells (padding
  * excluded): the groups between the end tiles and those of the two end tiles
- * (at q = 8 the kernels skip those between-group lookups that cannot change a
+ * (at q = 8 long folds and batches skip those lookups that cannot change a
  * cell; they are counted all the same);
  * splits[k] the terms of Eq. 1 inside a tile (split points within its own
  * columns and its own rows, which the finish covers 32 at a time, plus the

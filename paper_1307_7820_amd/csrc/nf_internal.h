@@ -66,6 +66,24 @@ __host__ __device__ inline long long tile_count(int NT) { return (long long)NT *
 // bit k = group k holds a column that rises by its pairing alone in this row.
 __host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
 
+// Shapes of the fused step: every group looked up and no marks; marks, one
+// workgroup a between chunk; marks, two workgroups a chunk.  The last two at q
+// = 8 only.
+enum : int { kStageAll = 0, kStageMarks = 1, kStageWide = 2 };
+// The shape for a single fold of NT tiles per side.  The marks cost the finish
+// one more ballot a row, on the chain that bounds a short fold, and spare a long
+// one four lookups in five; the lines cross between 85 and 94 tiles (MI355X, all
+// groups against marks: n = 500 92.7 and 98.9 us, 3300 638 and 671, 5400 1103
+// and 1158, 6000 1330 and 1298, 8000 2203 and 2053).  Several folds in a step are
+// bound by the work, not by the chain, and take the marks at any length.
+constexpr int kMarkTiles = 88;
+__host__ __device__ constexpr int single_shape(int q, int NT, bool wide)
+{
+    return !sparse_between(q) ? kStageAll : wide ? kStageWide : NT >= kMarkTiles ? kStageMarks : kStageAll;
+}
+// The same for several folds in one step.
+__host__ __device__ constexpr int many_shape(int q) { return sparse_between(q) ? kStageMarks : kStageAll; }
+
 // A between chunk spans at least this many group tiles C when the step's work
 // allows: a chunk has fixed costs (R into LDS, the first words, its atomic
 // maxima).  With the marks a turn takes four or eight tiles and a short chunk
@@ -73,7 +91,7 @@ __host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
 // and 1346 us; n = 16000 7179, 7142 and 7112 us); without them a chunk's time
 // goes with its tiles, and more of them fill the chip (q = 4, n = 1283,
 // minimum 4 and 6: 293 and 312 us).
-__host__ __device__ constexpr int min_chunk_tiles(int q) { return sparse_between(q) ? 6 : 4; }
+__host__ __device__ constexpr int min_chunk_tiles(int shape) { return shape == kStageAll ? 4 : 6; }
 
 // Entry e of R for vectors of length q (Section 3.1): row h = e >> (q-1),
 // column c; the largest running total of v + v-bar, 0 at k = 0.
@@ -123,7 +141,7 @@ struct TileItem {
 // A + (stage parity) * max_slots.
 struct SingleSchedule {
     int NT = 0, target = 1;
-    int min_chunk = 1;  // min_chunk_tiles(q)
+    int min_chunk = 1;  // min_chunk_tiles(shape)
 
     __host__ __device__ int max_slots() const { return NT >= 5 ? NT - 4 : 0; }
     // chunks per tile of diagonal dd (0 when the diagonal has no between work)
@@ -190,10 +208,9 @@ static_assert(sizeof(TileWork) == 80, "TileWork layout");
 static_assert(sizeof(BetweenWork) == 80, "BetweenWork layout");
 
 // One fused wavefront step: ntile tile finishes and nbtw between chunks of
-// the next diagonal in one launch of kTileThreads-thread workgroups.  wide
-// (q = 8 only; ignored otherwise) gives each chunk two workgroups with half
-// the rows each.
-hipError_t launch_stage(int q, bool wide, const TileWork* titems, int ntile, const BetweenWork* bitems, int nbtw,
+// the next diagonal in one launch of kTileThreads-thread workgroups, in the
+// shape that the whole fill takes.
+hipError_t launch_stage(int q, int shape, const TileWork* titems, int ntile, const BetweenWork* bitems, int nbtw,
                         const uint8_t* R, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // Whether a single fold of length n at q runs the wide fused step: the tuned
 // choice of n's length bucket if one was tuned at this q, else n >= 8192 at

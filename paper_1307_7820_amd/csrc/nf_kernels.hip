@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 constexpr int kTileThreads = 512;
 static_assert(kTileThreads == 512, "the tile finish assigns roles to 8 wavefronts");
 
-template <int Q, bool kWalk>
+template <int Q, int kMarks>
 struct TileLds {
     static constexpr int G = groups_per_tile(Q);
     // the end tiles' words of a row fit the registers of a wavefront; for
@@ -743,7 +743,7 @@ struct TileLds {
     // split points below row i among them
     alignas(16) uint32_t W[8][64];
     // the finish marks the groups that a between-group lookup may skip (see LV)
-    static constexpr bool kSparse = sparse_between(Q);
+    static constexpr bool kSparse = kMarks > 0, kWalk = kMarks > 1;
     uint32_t K[kSparse ? 2 : 1][kSparse ? 64 : 1];  // the columns of row i that rise by their pairing alone
     alignas(16) uint16_t P[16][64][4];            // P(i, j) at [i / 4][j][i % 4]
     alignas(16) uint32_t EB[kPipe ? 64 : 1][kES];  // EB[i][e*G + k]: row word of row i, group k of end tile e
@@ -768,13 +768,15 @@ __device__ __forceinline__ uint32_t above(uint32_t pair, uint32_t x)
 }
 
 // The finish of one tile by kTileThreads threads.  R is copied from Rg
-// (global) into Rl.  kWalk: the lookup wavefronts walk the marked groups only.
+// (global) into Rl.  kMarks: 1 writes the marks, 2 also has the lookup
+// wavefronts walk the marked groups only (kWalk).
 // flip (0 or 1): the roles of wavefronts w and w ^ 2 change places.
-template <int Q, bool kWalk>
+template <int Q, int kMarks>
 __device__ __forceinline__ void tile_body(const TileWork& it, int flip, uint8_t* Rl, const uint8_t* __restrict__ Rg,
-                                          TileLds<Q, kWalk>& s)
+                                          TileLds<Q, kMarks>& s)
 {
-    using Lds = TileLds<Q, kWalk>;
+    using Lds = TileLds<Q, kMarks>;
+    constexpr bool kWalk = Lds::kWalk;
     constexpr int M = Q - 1;
     constexpr int G = groups_per_tile(Q);
     constexpr int T = tile_size(Q);
@@ -1172,15 +1174,16 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(const TileWork* __restric
 {
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
-    constexpr bool kWalk = sparse_between(Q);
-    __shared__ __align__(16) TileLds<Q, kWalk> s;
-    tile_body<Q, kWalk>(items[blockIdx.x], __builtin_popcount(blockIdx.x >> 3) & 1, Rl, Rg, s);
+    constexpr int kMarks = sparse_between(Q) ? 2 : 0;
+    __shared__ __align__(16) TileLds<Q, kMarks> s;
+    tile_body<Q, kMarks>(items[blockIdx.x], __builtin_popcount(blockIdx.x >> 3) & 1, Rl, Rg, s);
 }
 
 // One wavefront step in one launch: workgroups [0, ntile) finish the tiles
 // of diagonal s, the rest run the between chunks of diagonal s+1 (which only
 // read diagonals <= s-1 and write the other half of the accumulators), one
-// workgroup each, or two in the wide shape (q = 8: kH of between_sparse).
+// workgroup each, or two in the wide shape (kH = 1 or 2 of between_sparse, q =
+// 8).  kH = 0: without marks, every group looked up.
 template <int Q, int kH>
 __global__ __launch_bounds__(kTileThreads) void k_stage(const TileWork* __restrict__ titems, int ntile,
                                                         const BetweenWork* __restrict__ bitems,
@@ -1189,19 +1192,19 @@ __global__ __launch_bounds__(kTileThreads) void k_stage(const TileWork* __restri
     constexpr int RSZ = 1 << (2 * (Q - 1));
     __shared__ __align__(16) uint8_t Rl[RSZ < 16 ? 16 : RSZ];
     const int b = blockIdx.x;
-    if constexpr (sparse_between(Q)) {
+    if constexpr (kH > 0) {
         __shared__ union Lds {
-            TileLds<Q, false> tile;
+            TileLds<Q, 1> tile;
             SparseLds<Q, kH> between;
         } s;
         if (b < ntile)
-            tile_body<Q, false>(titems[b], 0, Rl, Rg, s.tile);
+            tile_body<Q, 1>(titems[b], 0, Rl, Rg, s.tile);
         else
             between_sparse<Q, kH>(bitems[(b - ntile) / kH], (b - ntile) % kH, Rl, Rg, s.between);
     } else {
-        __shared__ __align__(16) TileLds<Q, false> s;
+        __shared__ __align__(16) TileLds<Q, 0> s;
         if (b < ntile) {
-            tile_body<Q, false>(titems[b], 0, Rl, Rg, s);
+            tile_body<Q, 0>(titems[b], 0, Rl, Rg, s);
         } else {
             load_R<RSZ>(Rl, Rg, kTileThreads);
             __syncthreads();
@@ -1401,15 +1404,17 @@ template <int Q>
 hipError_t stage_q(const TileWork* t, int nt, const BetweenWork* b, int nb, const uint8_t* R, hipStream_t s,
                    hipEvent_t e0, hipEvent_t e1)
 {
-    return launch_k(k_stage<Q, 1>, dim3(nt + nb), dim3(kTileThreads), s, e0, e1, t, nt, b, R);
+    return launch_k(k_stage<Q, 0>, dim3(nt + nb), dim3(kTileThreads), s, e0, e1, t, nt, b, R);
 }
 }  // namespace
 
-hipError_t launch_stage(int q, bool wide, const TileWork* titems, int ntile, const BetweenWork* bitems, int nbtw,
+hipError_t launch_stage(int q, int shape, const TileWork* titems, int ntile, const BetweenWork* bitems, int nbtw,
                         const uint8_t* R, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     if (ntile + nbtw <= 0) return hipSuccess;
-    if (wide && q == 8)
+    if (shape == kStageMarks && q == 8)
+        return launch_k(k_stage<8, 1>, dim3(ntile + nbtw), dim3(kTileThreads), s, e0, e1, titems, ntile, bitems, R);
+    if (shape == kStageWide && q == 8)
         return launch_k(k_stage<8, 2>, dim3(ntile + 2 * nbtw), dim3(kTileThreads), s, e0, e1, titems, ntile, bitems, R);
     switch (q) {
     case 1: return stage_q<1>(titems, ntile, bitems, nbtw, R, s, e0, e1);

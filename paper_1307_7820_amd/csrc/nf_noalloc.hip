@@ -157,7 +157,8 @@ extern "C" int nf_fold_dev_noalloc(const uint8_t* d_codes, int n, int q, int32_t
     SingleSchedule S;
     S.NT = g.NT;
     S.target = between_target(n, q);
-    S.min_chunk = min_chunk_tiles(q);
+    const int shape = single_shape(q, g.NT, stage_wide(n, q));
+    S.min_chunk = min_chunk_tiles(shape);
     const Layout L = layout(g, S, q);
     if (L.total > (size_t)NF_NOALLOC_SCRATCH_BYTES)
         return fail(NF_E_NOMEM,
@@ -197,9 +198,8 @@ extern "C" int nf_fold_dev_noalloc(const uint8_t* d_codes, int n, int q, int32_t
                        n16, nzero, q, R);
     HIPCHK(hipGetLastError());
     HIPCHK(launch_diag_codes(q, diag, S.NT, d_codes, n, s));
-    const bool wide = stage_wide(n, q);
     for (int sg = 1; sg < S.NT; ++sg)
-        HIPCHK(launch_stage(q, wide, tiles + S.finish_offset(sg), S.finishes(sg), btw + S.between_offset(sg),
+        HIPCHK(launch_stage(q, shape, tiles + S.finish_offset(sg), S.finishes(sg), btw + S.between_offset(sg),
                             S.between_count(sg), R, s));
     if (d_S && n > 0) HIPCHK(launch_expand(fd.F, g.ld, n, d_S, s, d_score));
     else if (d_score) HIPCHK(launch_scores(fdp, 1, d_score, s));

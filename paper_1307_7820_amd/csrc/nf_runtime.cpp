@@ -478,7 +478,7 @@ static int enqueue_fused_steps(Plan& p, hipStream_t s)
     if (rc) return rc;
     const Schedule& sc = p.sc;
     for (int sg = 1; sg < sc.stages; ++sg)
-        HIPCHK(launch_stage(p.q, p.wide, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg],
+        HIPCHK(launch_stage(p.q, p.shape, (const TileWork*)p.d_tile.p + sc.tile_off[sg], sc.tile_cnt[sg],
                             (const BetweenWork*)p.d_btw.p + sc.btw_off[sg], sc.btw_cnt[sg], R, s));
     return NF_OK;
 }
@@ -612,7 +612,7 @@ int plan_profile(Plan& p, hipStream_t s, int reps, nf_kernel_profile_t* out)
                 if (fused && sg >= 1) {
                     if (sc.tile_cnt[sg] + sc.btw_cnt[sg] == 0) continue;
                     if (!pair(a, b)) return fail(NF_E_DEVICE, "event creation failed");
-                    HIPCHK(launch_stage(p.q, p.wide, tw, sc.tile_cnt[sg], bw, sc.btw_cnt[sg], R, s, a, b));
+                    HIPCHK(launch_stage(p.q, p.shape, tw, sc.tile_cnt[sg], bw, sc.btw_cnt[sg], R, s, a, b));
                     recs.push_back({3, a, b, tile_lk[sg] + btw_lk[sg], tile_sp[sg], tile_cells[sg]});
                     continue;
                 }
@@ -706,7 +706,8 @@ int make_plan(const std::vector<int>& ns, int q, std::unique_ptr<Plan>& out, int
     if (p->plain) p->mode = kModeStaged;  // the fused step has the lookup built in
     p->target = target > 0 ? target : between_target(ns.size() == 1 ? ns[0] : -1, q);
     p->wide = ns.size() == 1 && q == 8 && (wide >= 0 ? wide > 0 : stage_wide(ns[0], q));
-    build_schedule(NTs, p->target, min_chunk_tiles(q), p->sc);
+    p->shape = ns.size() == 1 ? single_shape(q, NTs[0], p->wide) : many_shape(q);
+    build_schedule(NTs, p->target, min_chunk_tiles(p->shape), p->sc);
     if ((p->perturb = perturb_seed())) perturb_schedule(p->sc, p->perturb);
     int rc = plan_allocate(*p);
     if (rc) return rc;
@@ -1066,8 +1067,8 @@ extern "C" int nf_test_schedule(const int* NTs, int count, int target, char* msg
     for (int x : v)
         if (x < 1) return NF_E_INVAL;
     std::string err;
-    for (int q : {4, 8}) {  // both minimum chunk sizes
-        const int m = nf::min_chunk_tiles(q);
+    for (int shape : {nf::kStageAll, nf::kStageMarks}) {  // both minimum chunk sizes
+        const int m = nf::min_chunk_tiles(shape);
         if (err.empty()) err = nf::check_schedule(v, target, m);
         if (err.empty() && count == 1 && !nf::perturb_seed()) err = nf::check_single_schedule(v[0], target, m);
     }

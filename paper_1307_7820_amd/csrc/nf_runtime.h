@@ -101,7 +101,8 @@ struct Plan {
     int mode = kModeStaged;
     bool plain = false;  // between-group work by the plain recurrence (NF_BETWEEN=plain)
     int target = 0;      // between chunks per wavefront step the schedule was built for
-    bool wide = false;   // fused steps in the wide shape (two workgroups a between chunk at q = 8)
+    int shape = kStageAll;  // of the fused steps
+    bool wide = false;      // the fused steps' shape is kStageWide
     unsigned perturb = 0;  // test: seed of the shuffled item order and staged delays (0: none)
     std::vector<Geom> geom;
     std::vector<FoldDesc> h_folds;
@@ -175,7 +176,7 @@ int plan_mode_for(const std::vector<int>& NTs);
 bool plain_between_for(int q);
 int plan_profile(Plan& p, hipStream_t s, int reps, nf_kernel_profile_t* out);
 // target > 0 fixes the between chunks per step; wide < 0 takes stage_wide's
-// choice for a single fold (batches always run the default fused step).
+// choice for a single fold (batches never run the wide fused step).
 int make_plan(const std::vector<int>& ns, int q, std::unique_ptr<Plan>& out, int target = 0, int wide = -1);
 int single_plan(int n, int q, Plan** out, int target = 0, int wide = -1);
 int autotune_lookup(int n);

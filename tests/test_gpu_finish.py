@@ -75,3 +75,30 @@ def test_walked_end_tiles(nf, monkeypatch, n):
         want = oracle.fold_table(s)
         assert scores[k] == int(want[0, n - 1]), (k, n)
         assert np.array_equal(tables[k], want), (k, n)
+
+
+@pytest.mark.parametrize("n", [5567, 5568])
+def test_short_and_long_single_folds(nf, n):
+    """A single fold at q = 8 looks every group up below 88 tiles per side and
+    only the marked ones from there on: both sides of the line."""
+    s = gen.stem_sequence(n, [82, n])
+    score, T = nf.nf_fold(s, 8, table=True)
+    want = oracle.fold_table(s)
+    assert score == int(want[0, n - 1])
+    assert np.array_equal(T, want)
+
+
+@pytest.mark.parametrize("target", ["1", "37", "4096"])
+@pytest.mark.parametrize("n", [383, 1090])
+def test_marks_in_fused_batches(nf, monkeypatch, n, target):
+    """Several folds in a fused step take the marks at any length: chunks of one
+    to many tiles, every table against the oracle's."""
+    monkeypatch.setenv("NF_MODE", "fused")
+    monkeypatch.setenv("NF_BETWEEN_TARGET", target)
+    seqs = [gen.iid_sequence(n, [83, n]), gen.stem_sequence(n, [84, n]), ("GGGAAACCCUUU" * n)[:n],
+            gen.iid_sequence(n, [85, n], (0.5, 0.0, 0.0, 0.5)), "C" * (n // 2) + "G" * (n - n // 2)]
+    scores, tables = nf.nf_fold_batch(seqs, q=8, tables=True)
+    for k, s in enumerate(seqs):
+        want = oracle.fold_table(s)
+        assert scores[k] == int(want[0, n - 1]), (k, n, target)
+        assert np.array_equal(tables[k], want), (k, n, target)
