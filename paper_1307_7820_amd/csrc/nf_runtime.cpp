@@ -688,7 +688,12 @@ int plan_enqueue_steps(Plan& p, hipStream_t s)
     // steps go out one by one (MI355X, 7 steps 104 -> 98 us), many as a graph
     // that leaves the host free
     constexpr int kDirectStages = 16;
-    if (!use_graphs() || p.sc.stages <= kDirectStages) return enqueue_fused_steps(p, s);
+    if (!use_graphs()) return enqueue_fused_steps(p, s);
+    // on a stream that is being captured every length goes the same way: a
+    // recorded launch would hold the workspace's pointers past the call
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (p.sc.stages <= kDirectStages && cap == hipStreamCaptureStatusNone) return enqueue_fused_steps(p, s);
     return replay(p, p.steps_graph, p.steps_exec, enqueue_fused_steps, s);
 }
 
