@@ -61,10 +61,16 @@ __host__ __device__ inline long long tile_index(int NT, int A, int d)
 __host__ __device__ inline long long tile_count(int NT) { return (long long)NT * (NT + 1) / 2; }
 
 // Whether the between-group lookups at q skip the groups that the finish
-// leaves unmarked (q = 8, the default width).  The marks lie behind the column
-// blocks: for tile (A, B), at 64 * tile_index(NT, A, B - A), one byte per row,
-// bit k = group k holds a column that rises by its pairing alone in this row.
+// leaves unmarked (q = 8, the default width).  The marks of tile (A, B) are one
+// byte per row, bit k = group k holds a column that rises by its pairing alone
+// in this row.  They take no memory of their own: they lie in the table below
+// its main-diagonal tiles, where there are no cells.  Those of tile row A are
+// in table row mark_row(NT, A), 64 (T = 64) bytes per tile from byte 64 (B - A)
+// on.  The tile rows A = 64 k .. 64 k + 63 share tile row NT-1-k of the table,
+// whose rows have 128 (NT-1-k) bytes left of the main diagonal; their marks end
+// at byte 64 (NT - 64 k) at most, which is no more for NT >= 2.
 __host__ __device__ constexpr bool sparse_between(int q) { return q == 8; }
+__host__ __device__ constexpr long long mark_row(int NT, int A) { return 64ll * (NT - 1 - (A >> 6)) + (A & 63); }
 
 // Shapes of the fused step: every group looked up and no marks; marks, one
 // workgroup a between chunk; marks, two workgroups a chunk.  The last two at q
@@ -110,9 +116,9 @@ __host__ __device__ inline uint8_t r_entry(int q, int e)
 // One sequence being folded.  All pointers are device pointers.
 struct FoldDesc {
     const uint8_t* codes;  // NT*T + 64 bytes: base codes A0 C1 G2 U3, zero padding
-    int16_t* F;            // ld x ld table of F(a, b), ld = NT*T
+    int16_t* F;            // ld x ld table of F(a, b), ld = NT*T; the marks below its main-diagonal tiles
     uint32_t* RS;          // row blocks, tile_count(NT) * row_words(q)
-    uint32_t* CS;          // column blocks, tile_count(NT) * state_words(q), then the marks (sparse_between)
+    uint32_t* CS;          // column blocks, tile_count(NT) * state_words(q)
     int n, NT, ld, pad;
 };
 

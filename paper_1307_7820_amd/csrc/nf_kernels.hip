@@ -552,7 +552,7 @@ __device__ __forceinline__ void between_sparse(const BetweenWork& it, int half, 
     const int r0 = 32 * half + NR * wave;
     const NF_GLOBAL char* RSr = (const NF_GLOBAL char*)it.f.RS;
     const NF_GLOBAL char* CSr = (const NF_GLOBAL char*)it.f.CS;
-    const NF_GLOBAL char* LV = (const NF_GLOBAL char*)(it.f.CS + tile_count(NT) * SW);
+    const NF_GLOBAL char* LV = (const NF_GLOBAL char*)(it.f.F + mark_row(NT, A) * it.f.ld);
     issue_R<RSZ>(Rl, Rg, kBetweenThreads);
 
     // The words of the tiles C .. C+NC-1.  Tile numbers and byte offsets fit 32
@@ -583,7 +583,7 @@ __device__ __forceinline__ void between_sparse(const BetweenWork& it, int half, 
             if (C + kH * p < c1)
                 roww[p] = *(const NF_GLOBAL uint32_t*)(RSr + ((kH == 2 ? lane_index(d) : index(A, d)) * 2048u + roff));
         }
-        mark = *(const NF_GLOBAL uint8_t*)(LV + (lane_index(min(C + mq, c1 - 1) - A) * 64u + moff));
+        mark = *(const NF_GLOBAL uint8_t*)(LV + ((uint32_t)(min(C + mq, c1 - 1) - A) * 64u + moff));
     };
     uint32_t acc[NR];
 #pragma unroll
@@ -998,9 +998,9 @@ __device__ __forceinline__ void tile_body(const TileWork& it, int flip, uint8_t*
                     cw[u] = (CSr + tile_index(f.NT, e == 0 ? A + 1 : B - 1, e == 0 ? d - 1 : 1) * SW + k * 64)[(unsigned)lane];
             }
             if constexpr (kWalk) {
-                const NF_GLOBAL uint8_t* LV = (const NF_GLOBAL uint8_t*)(CSr + tile_count(f.NT) * SW);
-                const uint32_t k0 = d >= 2 ? (LV + tile_index(f.NT, A, 1) * 64)[(unsigned)lane] : 0u;
-                const uint32_t k1 = d >= 3 ? (LV + tile_index(f.NT, A, d - 1) * 64)[(unsigned)lane] : 0u;
+                const NF_GLOBAL uint8_t* LV = (const NF_GLOBAL uint8_t*)(F + mark_row(f.NT, A) * ld);
+                const uint32_t k0 = d >= 2 ? (LV + 64)[(unsigned)lane] : 0u;
+                const uint32_t k1 = d >= 3 ? (LV + (d - 1) * 64)[(unsigned)lane] : 0u;
                 marks = k0 | (k1 << G);
             }
             m0 = maximum(15);
@@ -1111,7 +1111,7 @@ __device__ __forceinline__ void tile_body(const TileWork& it, int flip, uint8_t*
             NF_GLOBAL int16_t* Fw = (NF_GLOBAL int16_t*)f.F;
             NF_GLOBAL uint32_t* CSw = (NF_GLOBAL uint32_t*)(f.CS + t_idx * SW);
             uint32_t cbits = 0;  // the rows' bits at this column, the last row in bit 0
-            NF_GLOBAL uint32_t* LVw = (NF_GLOBAL uint32_t*)(f.CS + tile_count(f.NT) * SW) + t_idx * 16;
+            [[maybe_unused]] NF_GLOBAL uint32_t* LVw = (NF_GLOBAL uint32_t*)(Fw + mark_row(f.NT, A) * ld) + d * 16;
 #pragma unroll 2
             for (int b = 15; b >= 0; --b) {
                 if constexpr (Lds::kSparse) {

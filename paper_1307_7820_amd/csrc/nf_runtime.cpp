@@ -203,7 +203,6 @@ Geom make_geom(int n, int q)
     g.F_bytes = up((size_t)g.ld * g.ld * sizeof(int16_t));
     g.rs_bytes = up((size_t)tile_count(g.NT) * row_words(q) * sizeof(uint32_t));
     g.cs_bytes = up((size_t)tile_count(g.NT) * state_words(q) * sizeof(uint32_t));
-    if (sparse_between(q)) g.cs_bytes += up((size_t)tile_count(g.NT) * 64);  // the marks
     g.bytes = g.codes_bytes + g.F_bytes + g.rs_bytes + g.cs_bytes;
     return g;
 }
@@ -1065,6 +1064,19 @@ std::string check_single_schedule(int NT, int target, int min_chunk)
 }  // namespace nf
 
 // Test hook (include/nf_test.h): host-only check of the wavefront schedule.
+extern "C" int nf_test_marks(int NT)
+{
+    if (NT < 1 || NT > 1024) return NF_E_INVAL;
+    std::vector<long long> used((size_t)NT * 64, 0);  // per table row: one past the last byte of a tile row's marks
+    for (int A = 0; A + 1 < NT; ++A) {
+        const long long r = nf::mark_row(NT, A);
+        if (r < 0 || r >= (long long)NT * 64 || used[r] != 0) return 1;  // a table row holds one tile row's
+        used[r] = 64ll * (NT - 1 - A) + 64;                              // tiles (A, A+1) .. (A, NT-1)
+        if (used[r] > r / 64 * 64 * (long long)sizeof(int16_t)) return 1;
+    }
+    return NF_OK;
+}
+
 extern "C" int nf_test_schedule(const int* NTs, int count, int target, char* msg, int cap)
 {
     if (count < 0 || (count > 0 && !NTs) || target < 1) return NF_E_INVAL;
