@@ -1,6 +1,6 @@
 /*
  * nf_test.h -- test hooks of libnf.so, outside the folding ABI of nf.h.
- * nf_test_schedule, nf_test_marks and nf_test_set_perturb are host-only;
+ * nf_test_schedule and nf_test_set_perturb are host-only;
  * nf_test_packed_state runs a fold on the GPU.
  */
 #ifndef NF_TEST_H
@@ -24,7 +24,10 @@ extern "C" {
  * reads; no two tiles of a stage sharing a slot; slot halves alternating by
  * stage.  For a single fold (count = 1) it also checks that the closed form
  * of the schedule that the allocation-free entry point evaluates on the
- * device gives the same items, in the same order and slots.  Under a
+ * device gives the same items, in the same order and slots, and the place of
+ * the marks of q = 8 in the fold's table: no two off-diagonal tiles share a
+ * byte, and every byte lies left of the main-diagonal tile of its table row
+ * (NT <= 1024).  Under a
  * perturbation seed (nf_test_set_perturb) the schedule is shuffled as plans
  * shuffle theirs before it is checked, and the closed form is not compared
  * (its order is the unperturbed one).  Returns 0 when
@@ -44,13 +47,6 @@ int nf_test_schedule(const int* NTs, int count, int target, char* msg, int cap);
  * result may change.  seed = 0 turns it off.  Plans are cached per seed;
  * nf_shutdown drops them.  Returns NF_OK. */
 int nf_test_set_perturb(unsigned seed);
-
-/* nf_test_marks
- * Check the place of the marks (q = 8) in the table of a fold of NT >= 1 tiles
- * per side: no two off-diagonal tiles share a byte, and every byte lies left of
- * the main-diagonal tile of its table row.  Host-only.  Returns 0 when it holds,
- * 1 when not, NF_E_INVAL for NT outside 1..1024. */
-int nf_test_marks(int NT);
 
 /* nf_test_packed_state
  * Fold seq[0..n) as nf_fold does (q in 1..9, explicit; n >= 2) and copy out

@@ -1022,6 +1022,20 @@ std::string check_schedule(const std::vector<int>& NTs, int target, int min_chun
     return "";
 }
 
+// The place of the marks in the table of a fold of NT tiles per side (see
+// mark_row): a table row holds those of one tile row, left of the main diagonal.
+std::string check_marks(int NT)
+{
+    std::vector<char> used((size_t)NT * 64, 0);
+    for (int A = 0; A + 1 < NT; ++A) {
+        const long long r = mark_row(NT, A), end = 64ll * (NT - A);  // tiles (A, A+1) .. (A, NT-1)
+        if (r < 0 || r >= (long long)NT * 64 || used[r] || end > r / 64 * 64 * (long long)sizeof(int16_t))
+            return "marks of NT " + std::to_string(NT) + " tile row " + std::to_string(A);
+        used[r] = 1;
+    }
+    return "";
+}
+
 // The closed form SingleSchedule, which the allocation-free entry point
 // evaluates on the device, against build_schedule for one fold: the same
 // items in the same order, and the same slot count.
@@ -1064,19 +1078,6 @@ std::string check_single_schedule(int NT, int target, int min_chunk)
 }  // namespace nf
 
 // Test hook (include/nf_test.h): host-only check of the wavefront schedule.
-extern "C" int nf_test_marks(int NT)
-{
-    if (NT < 1 || NT > 1024) return NF_E_INVAL;
-    std::vector<long long> used((size_t)NT * 64, 0);  // per table row: one past the last byte of a tile row's marks
-    for (int A = 0; A + 1 < NT; ++A) {
-        const long long r = nf::mark_row(NT, A);
-        if (r < 0 || r >= (long long)NT * 64 || used[r] != 0) return 1;  // a table row holds one tile row's
-        used[r] = 64ll * (NT - 1 - A) + 64;                              // tiles (A, A+1) .. (A, NT-1)
-        if (used[r] > r / 64 * 64 * (long long)sizeof(int16_t)) return 1;
-    }
-    return NF_OK;
-}
-
 extern "C" int nf_test_schedule(const int* NTs, int count, int target, char* msg, int cap)
 {
     if (count < 0 || (count > 0 && !NTs) || target < 1) return NF_E_INVAL;
@@ -1089,6 +1090,7 @@ extern "C" int nf_test_schedule(const int* NTs, int count, int target, char* msg
         if (err.empty()) err = nf::check_schedule(v, target, m);
         if (err.empty() && count == 1 && !nf::perturb_seed()) err = nf::check_single_schedule(v[0], target, m);
     }
+    if (err.empty() && count == 1 && v[0] <= 1024) err = nf::check_marks(v[0]);
     if (msg && cap > 0) snprintf(msg, (size_t)cap, "%s", err.c_str());
     return err.empty() ? NF_OK : 1;
 }

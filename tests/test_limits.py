@@ -1,6 +1,8 @@
 """What a fold takes on the device (host arithmetic, no GPU): the bytes a served
 fold is charged, and where the marks of q = 8 lie."""
 
+import ctypes
+
 import pytest
 
 
@@ -27,6 +29,7 @@ def test_fold_bytes_are_table_words_and_accumulators(nf, n, q):
 
 
 def test_marks_lie_in_the_unused_half_of_the_table(nf):
+    """The schedule hook checks their place for a single fold of NT tiles a side."""
+    msg = ctypes.create_string_buffer(256)
     for NT in list(range(1, 200)) + [251, 512, 1023, 1024]:
-        assert nf.load().nf_test_marks(NT) == 0, NT
-    assert nf.load().nf_test_marks(0) == nf.NF_E_INVAL
+        assert nf.load().nf_test_schedule((ctypes.c_int * 1)(NT), 1, 1024, msg, 256) == 0, (NT, msg.value)
