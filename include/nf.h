@@ -143,7 +143,10 @@ int nf_fold_structure(const char* seq, int n, int q, char* db_out);
  * d_S:     device int16 n*n table, layout above (may be NULL; when set the
  *          lower triangle is written as 0).
  * stream:  hipStream_t passed as void* (NULL = the null stream).
- * Work is enqueued on stream and the call returns without waiting.  The
+ * Work is enqueued on stream and the call returns without waiting.  A stream
+ * that is being captured into a graph is refused (NF_E_INVAL) before anything
+ * is enqueued or allocated: the fill may be a graph itself, which a capture
+ * does not record; nf_fold_dev_noalloc can be captured.  The
  * library keeps a per-(n,q) workspace; concurrent calls with the same (n,q)
  * on different streams must be ordered by the caller. */
 int nf_fold_dev(const uint8_t* d_codes, int n, int q, int32_t* d_score, int16_t* d_S, void* stream);
@@ -180,7 +183,8 @@ typedef struct nf_batch nf_batch;
  * of each q form one packed wavefront of their own: the groups run at once,
  * on streams forked from and joined back into the stream of nf_batch_run. */
 int nf_batch_create(const char* const* seqs, const int* ns, int count, int q, nf_batch** out);
-/* Enqueue one complete fill of every sequence in the batch on stream. */
+/* Enqueue one complete fill of every sequence in the batch on stream (not one
+ * that is being captured into a graph: NF_E_INVAL, as for nf_fold_dev). */
 int nf_batch_run(nf_batch* b, void* stream);
 /* Wait for the last run and copy the count scores to host memory. */
 int nf_batch_scores(nf_batch* b, int32_t* scores_out);

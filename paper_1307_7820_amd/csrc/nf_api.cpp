@@ -249,10 +249,11 @@ int nf_fold_dev(const uint8_t* d_codes, int n, int q, int32_t* d_score, int16_t*
     if ((rc = check_q(q))) return rc;
     if (!d_codes && n > 0) return fail(NF_E_INVAL, "d_codes is NULL");
     if ((rc = ensure_device())) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    if ((rc = refuse_capture(s, "nf_fold_dev"))) return rc;
     q = resolve_q(q, n);
     Plan* p = nullptr;
     if ((rc = single_plan(n, q, &p))) return rc;
-    hipStream_t s = (hipStream_t)stream;
     const Geom& g = p->geom[0];
     const bool table = d_S && n > 0;
     if (p->mode == kModeFused) {
@@ -346,6 +347,7 @@ int nf_batch_run(nf_batch* b, void* stream)
     int rc = ensure_device();
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
+    if ((rc = refuse_capture(s, "nf_batch_run"))) return rc;
     if (b->plans.size() > 1) HIPCHK(hipEventRecord(b->fork, s));
     for (size_t k = 1; k < b->plans.size(); ++k) {
         HIPCHK(hipStreamWaitEvent(b->side[k - 1], b->fork, 0));

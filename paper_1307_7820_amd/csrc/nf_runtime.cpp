@@ -643,6 +643,24 @@ int plan_profile(Plan& p, hipStream_t s, int reps, nf_kernel_profile_t* out)
     return NF_OK;
 }
 
+// A capture does not record the launch of a graph (HIP runs it at once, and the
+// caller's graph then replays without it), and a recorded launch of a step
+// would hold the workspace's pointers past the call.  So a call that fills by
+// graphs takes no stream that is being captured, at any length, and says so
+// before it has enqueued or allocated anything.
+int refuse_capture(hipStream_t s, const char* call)
+{
+    if (!use_graphs()) return NF_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();  // no answer: the launches will report what is wrong with the stream
+        return NF_OK;
+    }
+    if (cap == hipStreamCaptureStatusNone) return NF_OK;
+    return fail(NF_E_INVAL, "%s: the stream is being captured into a graph, which only nf_fold_dev_noalloc may be",
+                call);
+}
+
 // Replay the graph of what `enqueue` puts on a stream, captured at the first call.
 static int replay(Plan& p, hipGraph_t& graph, hipGraphExec_t& exec, int (*enqueue)(Plan&, hipStream_t), hipStream_t s)
 {
@@ -688,11 +706,7 @@ int plan_enqueue_steps(Plan& p, hipStream_t s)
     // that leaves the host free
     constexpr int kDirectStages = 16;
     if (!use_graphs()) return enqueue_fused_steps(p, s);
-    // on a stream that is being captured every length goes the same way: a
-    // recorded launch would hold the workspace's pointers past the call
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (p.sc.stages <= kDirectStages && cap == hipStreamCaptureStatusNone) return enqueue_fused_steps(p, s);
+    if (p.sc.stages <= kDirectStages) return enqueue_fused_steps(p, s);
     return replay(p, p.steps_graph, p.steps_exec, enqueue_fused_steps, s);
 }
 

@@ -164,6 +164,8 @@ int between_target(int n_single, int q);
 int plan_allocate(Plan& p);
 TileWork to_work(const TileItem& it, const std::vector<FoldDesc>& fd, int32_t* acc_base);
 BetweenWork to_work(const BetweenItem& it, const std::vector<FoldDesc>& fd, int32_t* acc_base);
+// NF_E_INVAL when s is being captured and fills run as graphs.
+int refuse_capture(hipStream_t s, const char* call);
 int plan_enqueue(Plan& p, hipStream_t s);
 int plan_enqueue_direct(Plan& p, hipStream_t s);
 // The fused steps of a single fold after its main-diagonal tiles, without the

@@ -1,0 +1,85 @@
+"""What libnf's host code asks of the HIP runtime, call by call, against a stub
+runtime on the CPU (tests/hip_stub.cpp) in a child process: no GPU is used."""
+
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_1307_7820_amd", "libnf.so")
+
+HEAD = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # found before the real runtime
+L = ctypes.CDLL(sys.argv[2])
+vp, c_int, c_sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
+stub.stub_log.restype = ctypes.c_char_p
+stub.stub_capture.argtypes = [vp]
+L.nf_last_error.restype = ctypes.c_char_p
+L.nf_fold_dev.argtypes = [vp, c_int, c_int, vp, vp, vp]
+L.nf_batch_create.argtypes = [vp, vp, c_int, c_int, vp]
+L.nf_batch_run.argtypes = [vp, vp]
+L.nf_batch_scores.argtypes = [vp, vp]
+L.nf_batch_destroy.argtypes = [vp]
+L.nf_batch_destroy.restype = None
+L.nf_fold_batch.argtypes = [vp, vp, c_int, c_int, vp, vp]
+mem = ctypes.create_string_buffer(1 << 16)
+score = c_int(0)
+STREAM = 0x1230
+
+def log():
+    out = stub.stub_log().decode().split("\\n")[:-1]
+    stub.stub_clear()
+    return out
+
+def fold(n, stream=STREAM):
+    return L.nf_fold_dev(mem, n, 8, ctypes.byref(score), None, stream)
+
+def batch(ns, q=8):
+    seqs = (ctypes.c_char_p * len(ns))(*[b"ACGU" * (n // 4) + b"A" * (n % 4) for n in ns])
+    h = vp()
+    assert L.nf_batch_create(seqs, (c_int * len(ns))(*ns), len(ns), q, ctypes.byref(h)) == 0, L.nf_last_error()
+    return h
+"""
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", os.path.join(ROOT, "tests", "hip_stub.cpp"), "-o", so])
+
+    def run(body, **env):
+        keep = {k: v for k, v in os.environ.items() if not k.startswith("NF_")}
+        subprocess.run([sys.executable, "-c", HEAD + textwrap.dedent(body), so, LIB], check=True, timeout=120,
+                       env=dict(keep, **env))
+    return run
+
+
+def test_a_stream_under_capture_is_refused_at_every_length(child):
+    """Before anything is enqueued or allocated, with a workspace at hand or
+    without; the streams beside it and the calls after it are served."""
+    child("""
+    for warm in (0, 1):
+        for n in (60, 500, 2000):
+            stub.stub_capture(STREAM)
+            log()
+            assert fold(n) == -1, (n, warm)
+            assert b"nf_fold_dev_noalloc" in L.nf_last_error()
+            work = [x for x in log() if x != "stream synchronize"]
+            assert work == [], (n, warm, work)
+            assert fold(n, STREAM + 16) == 0
+            stub.stub_capture(None)
+            log()
+            assert fold(n) == 0 and ("kernel" in log())
+    b = batch([60, 500])
+    stub.stub_capture(STREAM)
+    log()
+    assert L.nf_batch_run(b, STREAM) == -1 and log() == []
+    stub.stub_capture(None)
+    assert L.nf_batch_run(b, STREAM) == 0
+    L.nf_batch_destroy(b)
+    """)
