@@ -369,8 +369,13 @@ int plan_mode_for(const std::vector<int>& NTs)
 
 Plan::~Plan() { release_graph(); }
 
+// A graph may still run, behind a fold on device buffers that nothing has waited
+// for, and an event that has passed says nothing about what the runtime still
+// holds of a launch.  The buffers, freed next, wait for the device anyway.
 void Plan::release_graph()
 {
+    if (!exec && !steps_exec) return;
+    (void)hipDeviceSynchronize();
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     if (steps_exec) (void)hipGraphExecDestroy(steps_exec);

@@ -83,3 +83,33 @@ def test_a_stream_under_capture_is_refused_at_every_length(child):
     assert L.nf_batch_run(b, STREAM) == 0
     L.nf_batch_destroy(b)
     """)
+
+
+def test_a_graph_is_destroyed_only_when_the_device_is_idle(child):
+    """Between the last launch and the end of a graph lies a wait for the device:
+    a workspace dropped from the cache behind a fold that nothing waited for, a
+    batch destroyed after its run, the one-shot batch call."""
+    child("""
+    def ordered(calls):
+        busy, destroyed = False, 0
+        for c in calls:
+            if c in ("graph launch", "kernel"):
+                busy = True
+            elif c == "device synchronize":
+                busy = False
+            elif c in ("exec destroy", "graph destroy"):
+                destroyed += 1
+                assert not busy, calls
+        return destroyed
+    for n in (2000, 1900, 2100):
+        assert fold(n) == 0
+    assert ordered(log()) >= 4
+    for ns in ([60], [500, 700], [900] * 40, [1500] * 40):
+        b = batch(ns)
+        assert L.nf_batch_run(b, STREAM) == 0
+        L.nf_batch_destroy(b)
+        assert ordered(log()) == 2
+        seqs = (ctypes.c_char_p * len(ns))(*[b"A" * n for n in ns])
+        assert L.nf_fold_batch(seqs, (c_int * len(ns))(*ns), len(ns), 8, (c_int * len(ns))(), None) == 0
+        assert ordered(log()) == 2
+    """, NF_PLAN_CACHE_BYTES="1")
