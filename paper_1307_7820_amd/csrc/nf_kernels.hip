@@ -958,19 +958,26 @@ __device__ __forceinline__ void tile_body(const TileWork& it, int flip, uint8_t*
                     s.W[wave][4 * b + lane] = rows;
                     if constexpr (Lds::kSparse) s.K[wave][4 * b + lane] = firsts;
                 }
+                // The barrier below waits for the stores of W and K, not for the
+                // loads behind them: LDS accesses of a wavefront complete in
+                // order, and fetch() is four of them.  So these must stay
+                // behind the stores (the next line: no memory access may cross
+                // it) and be four on every way to the barrier (those of the
+                // last block are used after the blocks).  A test looks at the
+                // built code.
+                __asm__ volatile("" ::: "memory");
                 --b;
                 fetch(b >= 0 ? b : 0);
                 __builtin_amdgcn_sched_barrier(0);
                 E.ripple<W>(cE, up);
                 V.ripple<W>(cV, up);
                 if (W == 4) small = __ballot((E.large() | V.large()) != 0) == 0;
-                // the barrier waits for the store of W, not for the four loads
-                // behind it (LDS accesses of a wavefront complete in order)
                 __asm__ volatile("s_waitcnt lgkmcnt(4)\n\ts_barrier" ::: "memory");
             }
         };
         blocks(std::integral_constant<int, 4>{});
         blocks(std::integral_constant<int, 6>{});
+        __asm__ volatile("" ::"v"(pw.x), "v"(dw.x), "v"(sw.x), "v"(vw.x));  // (see above)
         // the slacks for the next step's tile of this column
 #pragma unroll
         for (int k = 0; k < 6; ++k) (k < 3 ? rsB : csB)[(k % 3) * 128 + 2 * j + h] = E.p[k];
