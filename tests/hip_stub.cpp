@@ -12,13 +12,16 @@ static hipStream_t g_captured = nullptr;  // a caller's stream that is being cap
 static hipStream_t g_own = nullptr;       // the library's stream under capture
 static long g_next = 1;
 
+static std::string g_grids;
+
 static void note(const char* what) { (g_log += what) += '\n'; }
 template <class T>
 static T handle() { return (T)(g_next++ * 4096); }
 
 extern "C" {
 const char* stub_log(void) { return g_log.c_str(); }
-void stub_clear(void) { g_log.clear(); }
+const char* stub_grids(void) { return g_grids.c_str(); }  // of the launches, one number each
+void stub_clear(void) { g_log.clear(); g_grids.clear(); }
 void stub_capture(void* s) { g_captured = (hipStream_t)s; }
 
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -32,7 +35,12 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* sh, hipStream_t* 
     *g = g_grid; *b = g_block; *sh = 0; *s = nullptr;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { note(g_own ? "record" : "kernel"); return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t, hipStream_t)
+{
+    note(g_own ? "record" : "kernel");
+    g_grids += std::to_string(grid.x) + ' ';
+    return hipSuccess;
+}
 hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) { note("kernel"); return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 

@@ -16,10 +16,13 @@ import ctypes, sys
 stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # found before the real runtime
 L = ctypes.CDLL(sys.argv[2])
 vp, c_int, c_sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
-stub.stub_log.restype = ctypes.c_char_p
+stub.stub_log.restype = stub.stub_grids.restype = ctypes.c_char_p
 stub.stub_capture.argtypes = [vp]
 L.nf_last_error.restype = ctypes.c_char_p
 L.nf_fold_dev.argtypes = [vp, c_int, c_int, vp, vp, vp]
+L.nf_submit.argtypes = [ctypes.c_char_p, c_int, c_int, c_int]
+L.nf_submit.restype = ctypes.c_int64
+L.nf_wait.argtypes = [ctypes.c_int64, c_int, vp, vp]
 L.nf_batch_create.argtypes = [vp, vp, c_int, c_int, vp]
 L.nf_batch_run.argtypes = [vp, vp]
 L.nf_batch_scores.argtypes = [vp, vp]
@@ -113,3 +116,28 @@ def test_a_graph_is_destroyed_only_when_the_device_is_idle(child):
         assert L.nf_fold_batch(seqs, (c_int * len(ns))(*ns), len(ns), 8, (c_int * len(ns))(), None) == 0
         assert ordered(log()) == 2
     """, NF_PLAN_CACHE_BYTES="1")
+
+
+@pytest.mark.parametrize("q,least", [(8, 6), (4, 4)])
+def test_served_steps_are_cut_like_batches(child, q, least):
+    """A chunk of a served step spans at least as many group tiles as one of a
+    batch's step: the workgroups of every step of one served fold."""
+    child("""
+    n, q, least = 2000, %d, %d
+    L.nf_serve_config.argtypes = [c_sz, c_int, c_int]
+    assert L.nf_serve_config(1 << 28, 0, 0) == 0
+    t = L.nf_submit(b"ACGU" * 500, n, q, 0)
+    assert t > 0, L.nf_last_error()
+    assert L.nf_wait(t, 20000, None, None) == 1
+    L.nf_shutdown()
+    grids = [int(x) for x in stub.stub_grids().split()]
+    NT = (n + 64) // 64
+    want = []
+    for s in range(1, NT):
+        dd, chunks = s + 1, 0
+        if 4 <= dd < NT:
+            chunk = max(least, -(-(NT - dd) * (dd - 3) // 1024))
+            chunks = (NT - dd) * -(-(dd - 3) // chunk)
+        want.append(NT - s + chunks)
+    assert grids[-NT - 1:] == [NT] + want + [1], (grids, want)
+    """ % (q, least))
