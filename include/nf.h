@@ -261,9 +261,8 @@ int nf_poll_ex(int64_t ticket, int timeout_ms, int32_t* score_out, int16_t* S_ou
 /* Engine counters: admitted, completed, rejected requests, device steps run,
  * the largest number of budget bytes ever held by active folds, and how many
  * steps ran fused (one launch per q holding the step's finishes and between
- * work, as nf_fold does; the others ran staged, on two streams).  A step is
- * fused while it holds at most 208 tiles to finish, unless NF_MODE (read when
- * the engine starts) forces one form. */
+ * work, as nf_fold does; the others ran staged, on two streams).  Every step is
+ * fused unless NF_MODE=staged was set when the engine started. */
 typedef struct {
     int64_t submitted, admitted, completed, rejected, steps;
     int64_t active, pending;

@@ -80,14 +80,19 @@ enum : int { kStageAll = 0, kStageMarks = 1, kStageWide = 2 };
 // one more ballot a row, on the chain that bounds a short fold, and spare a long
 // one four lookups in five; the lines cross between 85 and 94 tiles (MI355X, all
 // groups against marks: n = 500 92.7 and 98.9 us, 3300 638 and 671, 5400 1103
-// and 1158, 6000 1330 and 1298, 8000 2203 and 2053).  Several folds in a step are
-// bound by the work, not by the chain, and take the marks at any length.
+// and 1158, 6000 1330 and 1298, 8000 2203 and 2053).
 constexpr int kMarkTiles = 88;
 __host__ __device__ constexpr int single_shape(int q, int NT, bool wide)
 {
     return !sparse_between(q) ? kStageAll : wide ? kStageWide : NT >= kMarkTiles ? kStageMarks : kStageAll;
 }
-// The same for several folds in one step.
+// The same for several folds in one step, fused, staged or served: one shape,
+// since a fold of the serving engine keeps its words from step to step.  Folds
+// by the hundred are bound by the work and gain (4096 of 50..2000 bases 10.7 ->
+// 9.2 ms).  A fused batch of a few is bound by its chain like a single fold and
+// pays for the marks until its lookups outweigh that (MI355X, marks and all
+// groups: 2 folds of 100..700 bases 143 and 135 us, 16 of them 148 and 141; 8 of
+// 1000..2000 432 and 417; of 3000..3300 2 folds 686 and 667, 4 folds 743 and 779).
 __host__ __device__ constexpr int many_shape(int q) { return sparse_between(q) ? kStageMarks : kStageAll; }
 
 // A between chunk spans at least this many group tiles C when the step's work

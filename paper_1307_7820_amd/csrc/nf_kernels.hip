@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kBetweenThreads) void k_between(const BetweenWork* 
 // n = 3001 926 -> 762 us.)
 //
 // Staged steps hold hundreds to thousands of finishes, four to a CU, and are
-// bound by the VALU (77% busy) and not by this chain.  There, at q = 8, the
+// bound by the VALU (over 70% busy) and not by this chain.  There, at q = 8, the
 // lookup wavefronts walk the marked groups as between_sparse does (kWalk): 8
 // LDS reads and 18 VALU instructions for up to four groups against 20 and 40
 // for all sixteen; and every other workgroup gives the rows to wavefronts 2 and
@@ -742,7 +742,7 @@ struct TileLds {
     // [4], [5]: dL(i, .) of the split points 0..31 and 32..63; [6], [7]: the
     // split points below row i among them
     alignas(16) uint32_t W[8][64];
-    // the finish marks the groups that a between-group lookup may skip (see LV)
+    // the finish marks the groups that a between-group lookup may skip (see mark_row)
     static constexpr bool kSparse = kMarks > 0, kWalk = kMarks > 1;
     uint32_t K[kSparse ? 2 : 1][kSparse ? 64 : 1];  // the columns of row i that rise by their pairing alone
     alignas(16) uint16_t P[16][64][4];            // P(i, j) at [i / 4][j][i % 4]
