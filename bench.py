@@ -42,6 +42,9 @@ OPS_PER_TERM = 0.5                            # an Eq. 1 term inside a tile: 16 
 HBM_BYTES_PER_LOOKUP = 6.0 / 64
 TUNE_REPS = 5                                 # folds per candidate when the headline q and chunk target are tuned
 PEAK_HBM = 8.0e12
+PEAK_VALU_ISSUE = 256 * 2.4e9                 # wave instructions/s: one a clock and CU (4 SIMDs, 4 clocks each)
+# what roofline_times counts as work
+COUNTED = "all lookups of the method; at q = 8 long folds, batches and served steps skip about four in five of them"
 
 
 def log(*a):
@@ -89,22 +92,23 @@ def kernels_source_hash() -> str:
         return hashlib.sha256(fh.read()).hexdigest()[:16]
 
 
-def traffic_bytes(kernel: str, q: int, n: int, target: int, wide: int):
-    """HBM bytes per launch of `kernel`, from the committed rocprofv3 counter
-    summary profiles/<kernel>_q<q>_<workload>_pmc.txt: FETCH_SIZE and
+def counted(kernel: str, q: int, n: int, target: int, wide: int):
+    """What the hardware counted per launch of `kernel`, from the committed
+    rocprofv3 counter summary profiles/<kernel>_q<q>_<workload>_pmc.txt, as
+    (HBM bytes, VALU wave instructions).  The bytes are FETCH_SIZE and
     WRITE_SIZE (KiB per dispatch, separate runs), each scaled by what the same
-    counter reads for a plain device copy of known size.  The summary holds
-    one `traffic:` line per launch configuration measured; the one taken at
-    `target` between-group chunks per step and step shape `wide` (split
-    chunks write by atomic max, so the chunks change the bytes) is used.
-    None when there is no summary or no such line, or when the kernel source
-    has changed since the counters were taken (its hash is in the line)."""
+    counter reads for a plain device copy of known size; the instructions are
+    SQ_INSTS_VALU, what is really issued, without the lookups that are skipped.
+    The summary holds one `traffic:` line per launch configuration measured;
+    the one taken at `target` between-group chunks per step and step shape
+    `wide` (split chunks write by atomic max, so the chunks change the bytes) is
+    used.  None for either when there is no summary or no such line, or when
+    the kernel source has changed since the counters were taken (its hash is
+    in the line)."""
     wl = WORKLOAD_NAMES.get(n)
-    if wl is None:
-        return None
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "%s_q%d_%s_pmc.txt" % (kernel, q, wl))
-    if not os.path.exists(path):
-        return None
+    if wl is None or not os.path.exists(path):
+        return None, None
     with open(path) as fh:
         for line in fh:
             if not line.startswith("traffic:"):
@@ -115,11 +119,12 @@ def traffic_bytes(kernel: str, q: int, n: int, target: int, wide: int):
                     continue
                 if int(vals.get("target", "0")) != target or int(vals.get("wide", "0")) != int(wide):
                     continue
-                return 1024.0 * (float(vals["fetch_kib"]) * float(vals["fetch_scale"]) +
-                                 float(vals["write_kib"]) * float(vals["write_scale"]))
+                return (1024.0 * (float(vals["fetch_kib"]) * float(vals["fetch_scale"]) +
+                                  float(vals["write_kib"]) * float(vals["write_scale"])),
+                        float(vals["valu_insts"]) if "valu_insts" in vals else None)
             except (KeyError, ValueError):
                 continue
-    return None
+    return None, None
 
 
 def lds_ceiling(nf, q: int):
@@ -140,7 +145,8 @@ def roofline_times(lookups: float, terms: float, cells_out: float, seconds: floa
     every group looked up.  At q = 8 the kernels skip the groups whose splits
     cannot change a cell (four in five on these workloads), so achieved is the
     rate at which that work is dealt with, not the issue rate of the VALU, and
-    frac can pass 1; the SQ counters under profiles/ give how busy the units are."""
+    frac can pass 1.  How much of the VALU's issue the kernel really uses is
+    valu_issue_frac, from the instructions that the hardware counted."""
     t_valu = (OPS_PER_LOOKUP * lookups + OPS_PER_TERM * terms) / PEAK_VALU_LANE_OPS
     t_lds = lookups / lds_rate
     hbm_bytes = HBM_BYTES_PER_LOOKUP * lookups + 2.0 * cells_out
@@ -154,6 +160,7 @@ def roofline_times(lookups: float, terms: float, cells_out: float, seconds: floa
     else:
         out = {"bound": "hbm", "achieved": hbm_bytes / seconds / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s"}
     out["frac"] = out["achieved"] / out["peak"]
+    out["frac_counts"] = COUNTED
     out["t_valu_us"], out["t_lds_us"], out["t_hbm_us"], out["t_us"] = (1e6 * t_valu, 1e6 * t_lds, 1e6 * t_hbm,
                                                                       1e6 * seconds)
     out["algorithmic_hbm_bytes"] = hbm_bytes
@@ -179,13 +186,15 @@ def roofline(nf, codes, n, q, lds, reps=3):
     X = prof.splits[k] / prof.launches[k]
     C = prof.cells[k] / prof.launches[k]
     r = roofline_times(L, X, C, per_launch_s, lds["row_gathers_per_s"])
-    traffic = traffic_bytes(name, q, n, target, prof.wide)
+    traffic, issued = counted(name, q, n, target, prof.wide)
     out = {"kernel": name, "launches_per_fold": prof.launches[k] // reps,
            "avg_launch_us": 1e6 * per_launch_s,
            "per_kernel_ms_per_fold": {nf.KERNEL_NAMES[i]: prof.ms[i] / reps for i in ks},
            **r,
            "lookups_per_launch": L, "terms_per_launch": X, "cells_per_launch": C,
            "glookups_per_s": prof.lookups[k] / (prof.ms[k] / 1e3) / 1e9,
+           "valu_insts_per_launch": issued,
+           "valu_issue_frac": issued / per_launch_s / PEAK_VALU_ISSUE if issued else None,
            "traffic": traffic,
            "hbm_achieved_gbs": traffic / per_launch_s / 1e9 if traffic else None,
            "hbm_frac": traffic / per_launch_s / PEAK_HBM if traffic else None,
@@ -817,7 +826,8 @@ def main():
         "config": {"workload": "single iid uniform ACGU sequence, n=6000, two-vector Four-Russians fill",
                    "n": n, "q": q, "between_chunks_per_step": target, "autotuned": not args.q,
                    "tile": roof.get("tile"), "score": score},
-        "roofline": {k: roof[k] for k in ("bound", "achieved", "peak", "unit", "frac", "traffic")},
+        "roofline": {k: roof[k] for k in ("bound", "achieved", "peak", "unit", "frac", "frac_counts", "valu_issue_frac",
+                                          "traffic")},
         "roofline_detail": roof,
         "roofline_whole_fold": fold_roof,
         "lds_gather_ceiling": lds,
